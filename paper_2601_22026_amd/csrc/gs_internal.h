@@ -187,12 +187,12 @@ struct KeyPlace {
 // Position of the key of record r in tile (ty, tx) of its view: koff[r] plus
 // the tile's rank among the record's listed tiles, from the packed row spans
 // or (other boxes) the row table entry of row ty, found by binary search.
-__device__ __forceinline__ uint32_t key_slot(const KeyPlace &kp, uint32_t r, int ty, int tx) {
-    const uint2 rc = kp.rect[r], pk = kp.rspan[r];
+// rc, pk, base: the record's rect, rspan and koff entries.
+__device__ __forceinline__ uint32_t key_slot_of(const KeyPlace &kp, uint2 rc, uint2 pk, uint32_t base,
+                                                int ty, int tx) {
     const int x0 = (int)(rc.x & 0xFFFFu), y0 = (int)(rc.x >> 16);
     const int x1 = (int)(rc.y & 0xFFFFu), y1 = (int)(rc.y >> 16);
     const int rows = y1 - y0 + 1, cols = x1 - x0 + 1;
-    const uint32_t base = kp.koff[r];
     uint32_t rank = 0;
     if (rows <= kPackRows && cols <= kPackCols) {
         const int kr = ty - y0;
@@ -210,6 +210,9 @@ __device__ __forceinline__ uint32_t key_slot(const KeyPlace &kp, uint32_t r, int
         rank = e.y + (uint32_t)tx - (e.x >> 16);
     }
     return base + rank;
+}
+__device__ __forceinline__ uint32_t key_slot(const KeyPlace &kp, uint32_t r, int ty, int tx) {
+    return key_slot_of(kp, kp.rect[r], kp.rspan[r], kp.koff[r], ty, tx);
 }
 
 // ---- wave-level helpers shared by the adjoint passes ------------------------------

@@ -29,6 +29,8 @@
 // key's own position; a separate pass sums each record's keys (no atomics).
 // With 16-pixel tiles each wave covers an 8x8 quadrant of the tile and skips
 // the splats whose padded support ellipse misses it.
+#include <type_traits>
+
 #include "gs_internal.h"
 
 namespace gsf {
@@ -61,13 +63,6 @@ __device__ __forceinline__ bool splat_alpha(const float4 &a, const float4 &b, co
     return true;
 }
 
-// Threads of an adjoint workgroup: one wave per 8x8 or 16x16 tile (1 or 4 pixels
-// per lane), two waves per 32x32 tile (8 pixels per lane).  Each lane first sums
-// its own pixels' contributions, so the per-splat cross-lane reductions, the
-// bulk of the adjoint's VALU work, are shared by more pixels.
-template <int T>
-constexpr int bwd_threads() { return T == 32 ? 128 : 64; }
-
 // A record's c = (blue, tau, ix, iy): tau = -log2(255 o) is the alpha
 // threshold of the base-2 exponent, computed once by the projection.  The
 // padded half height of the support (where o e^power >= 1/255 can hold) is
@@ -80,20 +75,8 @@ __device__ __forceinline__ float quad_half_height(const float4 &e0) {
     return __builtin_amdgcn_sqrtf(e0.y * __builtin_amdgcn_rcpf(e0.z));
 }
 
-__device__ __forceinline__ float support_half_height(const float4 &e0) {
-    return sqrtf(e0.y / e0.z) + kBoxAbs;
-}
-
 typedef __attribute__((address_space(3))) void *lds_void_ptr;
 __device__ __forceinline__ lds_void_ptr lds_ptr(void *p) { return (lds_void_ptr)p; }
-
-// Whether rows with offsets [lo, lo + span] from a splat's mean can meet its
-// support of half height h (NaN-safe: only a definite miss returns false).
-// Rows farther away are skipped as a block: the per-pixel test would skip
-// every pair there.
-__device__ __forceinline__ bool rows_meet(float lo, float span, float h) {
-    return !(lo > h) && !(lo + span < -h);
-}
 
 __device__ __forceinline__ int view_of_tile(const ViewDesc *__restrict__ views, int nviews, int gt) {
     int v = 0;
@@ -133,48 +116,6 @@ __device__ __forceinline__ bool in_fovea(const float *__restrict__ gaze, int v, 
     if (!gaze) return true;
     const float dx = (float)x + 0.5f - gaze[2 * v], dy = (float)y + 0.5f - gaze[2 * v + 1];
     return dx * dx + dy * dy <= radius * radius;
-}
-
-// Sum of x over the 64 lanes of a wave, valid in lane 63: four row shifts
-// (DPP row_shr 1, 2, 4, 8) leave each 16-lane row's total in its lane 15, then
-// row_bcast:15 and row_bcast:31 fold the rows together.  All steps are VALU
-// instructions with DPP operands (no LDS traffic).
-
-// Sum over each 16-lane row, left in the row's last lane (15, 31, 47, 63).
-__device__ __forceinline__ float row_sum_lane15(float x) {
-    x += dpp_shift<0x111, 0xf>(x);   // row_shr:1
-    x += dpp_shift<0x112, 0xf>(x);   // row_shr:2
-    x += dpp_shift<0x114, 0xf>(x);   // row_shr:4
-    x += dpp_shift<0x118, 0xf>(x);   // row_shr:8
-    return x;
-}
-
-// Wave sums of two splats' nine per-lane terms a and b at once.  A
-// v_permlane32_swap per field halves the 18 values (lanes 0-31 then hold
-// splat a's partial sums, lanes 32-63 splat b's), a v_permlane16_swap per
-// pair of fields leaves one (splat, field) per 16-lane row, and a row sum
-// (four DPP adds) finishes: lane 15 of row 0 holds a's fields 0, 2, 4, 6, 8
-// in out[0..4], row 1 a's fields 1, 3, 5, 7 in out[0..3], rows 2 and 3 the
-// same of b.  24 VALU instructions per splat against 36 for nine row sums.
-// (Written as inline assembly: this compiler folds the two results of the
-// permlane-swap builtins into one when both feed the same expression.  The
-// swap is a register-only VALU operation; the s_nop gives it the two wait
-// states it needs after the VALU writes of its operands.)
-__device__ __forceinline__ float swap_add32(float x, float y) {
-    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(x), "+v"(y));
-    return x + y;
-}
-__device__ __forceinline__ float swap_add16(float x, float y) {
-    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(x), "+v"(y));
-    return x + y;
-}
-__device__ __forceinline__ void pair_sums(const float (&a)[9], const float (&b)[9], float (&out)[5]) {
-    float L[9];
-#pragma unroll
-    for (int f = 0; f < 9; f++) L[f] = swap_add32(a[f], b[f]);
-#pragma unroll
-    for (int k = 0; k < 4; k++) out[k] = row_sum_lane15(swap_add16(L[2 * k], L[2 * k + 1]));
-    out[4] = row_sum_lane15(swap_add16(L[8], 0.f));
 }
 
 // MODE 1 (checkpointed): also store (T, colour) of every pixel after each LDS
@@ -497,43 +438,68 @@ __global__ __launch_bounds__((fwd_threads<T, SPLIT>())) void k_render_fwd(
     }
 }
 
-// Per-splat gradient sums of one adjoint wave, for a block of R = 64
-// consecutive splats (stored as soon as a block is done, one lane per splat,
-// so that every lane of the wave stores): nine fields of R splats, plus one
-// word so that two waves' slots fall in different LDS banks.  A checkpointed
-// unit (one LDS batch of up to 64) stores once.
-template <int MODE>
-constexpr int kRing = 64;
-template <int MODE>
-constexpr int kGradSlot = 9 * kRing<MODE> + 1;
-static_assert(kRing<0> % 2 == 0 && kRing<1> % 2 == 0, "splat pairs stay within a block");
+// ---- adjoint ---------------------------------------------------------------------
+//
+// One wave per 8 x 8 block of the tile's pixels (T / 8 squared waves a
+// workgroup), one pixel per lane.  The tile's list is taken back to front in
+// chunks of 64 records, staged in LDS; each wave lists the chunk's splats that
+// reach its block and walks them eight at a time.  Per splat and pixel the
+// recurrence leaves two numbers: te = dL/d(opacity) (dL/dpower = o te) and wT =
+// alpha T.  Everything the splat's screen-space gradient needs from the block is
+// a contraction of these over the block's 64 pixels:
+//   sum te {1, u, v, u^2, u v, v^2}   (u, v: pixel offsets from the block's centre)
+//   sum wT {dL/dR, dL/dG, dL/dB}
+// whose right-hand factors do not depend on the splat.  Eight splats' te and wT
+// rows (16 x 64, through LDS) times that 64 x 9 matrix (in registers, laid out
+// once per unit) are sixteen v_mfma_f32_16x16x4_f32 in full FP32.  When a chunk
+// is done the blocks' sums are moved from their centres to each splat's mean and
+// added in the order of the blocks: no atomics, the same bits in every run.
+// (gfx950 issues no VALU work of other waves under an FP32 matrix instruction, 32
+// cycles each, so the products cost throughput: this form is for plans where the
+// length of the lists, not issue, sets the time.  One view of 128^2 with 1,000
+// Gaussians 71 -> 25 us, of 701 x 533 with 30,000 188 -> 72 us; on sixteen views
+// of 1920^2 it takes 2800 us where one wave per tile takes 1910.)
+constexpr int kAdjChunk = 64;    // records staged at a time
+constexpr int kAdjGroup = 8;     // splats per matrix product (two rows each)
+constexpr int kAdjRow = 68;      // row stride, floats: 16-byte reads of 16 rows fall in distinct banks
+constexpr int kAdjSec = kAdjChunk + 1;   // + the inert splat that pads a group
+
+template <int T>
+constexpr int adj_waves() { return (T / 8) * (T / 8); }
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+template <int T>
+struct AdjShared {
+    static constexpr int NW = adj_waves<T>();
+    float4 rec[2][4][kAdjSec];            // two chunks' records by section (a, b, c, ellipse)
+    uint2 key[2][3][kAdjChunk];           // their boxes, row spans, first key positions
+    alignas(16) float row[NW][2 * kAdjGroup * kAdjRow];
+    float sum[NW][kAdjChunk * 9];         // per splat of the chunk: the block's nine sums
+    uint64_t hit[NW];                     // splats of the chunk with sums
+    alignas(16) int list[NW][kAdjChunk + kAdjGroup];
+    uint32_t nmax[NW];
+};
 
 // Unit of adjoint work: the entries [us, ue) of launch tile ti's list (tm maps
 // it to its view and tile).  With
-// checkpoints (MODE 1) a unit is one LDS batch of B entries and starts from the
-// state the forward stored at the batch's end; otherwise a unit is the whole
+// checkpoints (MODE 1) a unit is one LDS batch of `batch` entries and starts from
+// the state the forward stored at the batch's end; otherwise a unit is the whole
 // list and starts from the final state.  MODE 2 reads each included pair's
 // transmittance from tstore instead of dividing.
-template <int T, int B, int MODE>
+template <int T, int MODE>
 __device__ __forceinline__ void render_bwd_unit(
     uint32_t ti, const TileMap &tm, uint32_t us, uint32_t ue, bool last_unit, const uint2 &rg,
-    const uint32_t *__restrict__ vals, SplatPtrs sp, const ViewDesc *__restrict__ views,
-    int nviews, const gsf_camera *__restrict__ cams, const float *__restrict__ tfinal,
-    const uint32_t *__restrict__ ncontrib, const float4 *__restrict__ fstate,
-    const float4 *__restrict__ ckpt, const float *__restrict__ tstore, const float *__restrict__ bg,
-    const float *__restrict__ dl, const KeyPlace &kp, float4 *s_a, float4 *s_b, float4 *s_c,
-    uint32_t *s_q, uint8_t *s_m, float *s_g, uint64_t *s_hit, float *s_h, uint32_t *s_nmax) {
+    uint32_t batch, const uint32_t *__restrict__ vals, SplatPtrs sp,
+    const ViewDesc *__restrict__ views, int nviews, const gsf_camera *__restrict__ cams,
+    const float *__restrict__ tfinal, const uint32_t *__restrict__ ncontrib,
+    const float4 *__restrict__ fstate, const float4 *__restrict__ ckpt,
+    const float *__restrict__ tstore, const float *__restrict__ bg, const float *__restrict__ dl,
+    const KeyPlace &kp, AdjShared<T> &sh) {
     constexpr bool CKPT = MODE == 1;
-    constexpr int TL = T == 8 ? 3 : T == 16 ? 4 : 5;
-    constexpr int R = kRing<MODE>, GS = kGradSlot<MODE>;
-    constexpr int NT = bwd_threads<T>();
-    constexpr int PPT = T * T / NT;
-    constexpr int ROWS = NT / T;
-    constexpr int NW = NT / 64;
-    // 16-pixel tiles: one wave, pixel block k = quadrant k of the tile (8 x 8),
-    // and a splat skips the quadrants its padded ellipse does not reach
-    constexpr bool QUAD = T == 16;
-    static_assert(!QUAD || (NT == 64 && PPT == 4), "quadrant layout: one wave, four blocks");
+    constexpr int NW = adj_waves<T>(), NT = 64 * NW;
+    constexpr int PARTS = NT >= 256 ? 1 : 256 / NT;   // 16-byte record pieces a thread stages per chunk
+    constexpr int QX = T / 8;                         // blocks per tile row
     int v, ty, tx;
     ViewDesc vd;
     launch_tile(ti, tm, views, nviews, T, v, vd, ty, tx);   // a tile with keys: valid
@@ -543,28 +509,383 @@ __device__ __forceinline__ void render_bwd_unit(
     // contributor, which the pixel state says)
     const bool live = !tm.gaze || fovea_tile_live(tm.gaze, v, tm.radius, vd.width, vd.height, T, tx, ty);
     const float disk_r = tm.gaze ? tm.radius * (float)vd.width : 0.f;
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const float *bgv = bg ? bg + 3 * v : cams[v].bg;
+    const size_t plane = (size_t)vd.width * vd.height;
+    const float *dimg = dl + 4 * (size_t)vd.pix_off;
+    const int bx = tx * T + (wave % QX) * 8, by = ty * T + (wave / QX) * 8;   // the block's first pixel
+
+    // gR: dL/dC-weighted colour behind the current splat, less gA Tf (the alpha
+    // plane's share), carried as one value since only that difference is used
+    const int x = bx + (lane & 7), y = by + (lane >> 3);
+    const float px = (float)x, py = (float)y;   // integer pixel; its centre's offset from a mean is splat_dx
+    const int pix = (y - ty * T) * T + (x - tx * T);   // the pixel's row-major index in the tile
+    float Tr = 1.f, Tf = 1.f, g0 = 0.f, g1 = 0.f, g2 = 0.f, gA = 0.f;
+    uint32_t nc = 0u;
+    const bool inside = live && x < vd.width && y < vd.height && in_fovea(tm.gaze, v, x, y, disk_r);
+    const size_t q = inside ? (size_t)y * vd.width + x : 0;
+    if (inside) {
+        Tf = tfinal[vd.pix_off + q];
+        nc = ncontrib[vd.pix_off + q];
+        g0 = dimg[q];
+        g1 = dimg[plane + q];
+        g2 = dimg[2 * plane + q];
+        gA = dimg[3 * plane + q];
+    }
+    // a pixel no splat reached passes no gradient, whatever its dL/dimage
+    // (which a fovea-culled loss may not have written): it starts at zero
+    if (nc == 0u) {
+        Tf = 1.f;
+        g0 = g1 = g2 = gA = 0.f;
+    }
+    float gR = Tf * (g0 * bgv[0] + g1 * bgv[1] + g2 * bgv[2]);
+    Tr = Tf;
+    if (CKPT && !last_unit && rg.x + nc > us) {
+        // colour behind the unit = final colour - colour accumulated at its end
+        const float4 fs = fstate[vd.pix_off + q];
+        const float4 cp = ckpt[(size_t)(ue / batch) * (T * T) + pix];
+        Tr = cp.x;
+        gR = gR + g0 * (fs.y - cp.y) + g1 * (fs.z - cp.z) + g2 * (fs.w - cp.w);
+    }
+    gR -= gA * Tf;
+    // the block's largest contributor count: a splat at or past it reaches no
+    // pixel of the block; and the tile's
+    uint32_t qmax = nc;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) qmax = max(qmax, (uint32_t)__shfl_xor((int)qmax, o, 64));
+    qmax = __builtin_amdgcn_readfirstlane(qmax);
+    float *const row = sh.row[wave];
+    row[lane] = g0;
+    row[64 + lane] = g1;
+    row[128 + lane] = g2;
+    if (lane == 0) sh.nmax[wave] = qmax;
+    if (tid < 6) {   // the inert splat of both buffers: power2 = 0 < tau = +inf, never included
+        sh.rec[tid & 1][tid >> 1][kAdjChunk] =
+            make_float4(0.f, tid >> 1 == 2 ? __builtin_inff() : 0.f, 0.f, 0.f);
+    }
+    __syncthreads();
+    uint32_t nmax = 0u;
+#pragma unroll
+    for (int w = 0; w < NW; w++) nmax = max(nmax, sh.nmax[w]);
+    const uint32_t top = min(ue, rg.x + nmax);
+
+    // Right-hand factor: lane (column j = lane & 15, k = lane >> 4) holds, for
+    // product m, column j of pixel 16 k + m: 1, u, v, u^2, u v, v^2 (exact in
+    // float: u, v are half-integers), then the pixel's dL/dR, dL/dG, dL/dB.
+    const int j = lane & 15, kq = lane >> 4;
+    float bq[16];
+    {
+        const float *gp = row + 64 * min(max(j - 6, 0), 2) + 16 * kq;
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const float vv = (float)(2 * kq + h) - 3.5f;
+            const float c0 = j == 0 ? 1.f : (j == 2 ? vv : (j == 5 ? vv * vv : 0.f));
+            const float c1 = j == 1 ? 1.f : (j == 4 ? vv : 0.f);
+            const float c2 = j == 3 ? 1.f : 0.f;
+#pragma unroll
+            for (int m = 0; m < 8; m++) {
+                const float u = (float)m - 3.5f;
+                const float poly = fmaf(fmaf(c2, u, c1), u, c0);
+                bq[8 * h + m] = j >= 6 && j < 9 ? gp[8 * h + m] : poly;
+            }
+        }
+    }
+    __builtin_amdgcn_wave_barrier();   // row is reused below
+
+    // Staging, from registers loaded a chunk ahead (record ids two ahead): thread
+    // (entry e = t / 4, piece t % 4) takes one 16-byte piece of a record and one
+    // of the key-slot lookup's three arrays.
+    uint32_t rid[PARTS];
+    float4 pre[PARTS];
+    uint2 kpre[PARTS];
+    auto fetch_ids = [&](uint32_t ce) {   // record ids of the chunk that ends at ce
+        const uint32_t cs = ce - us > (uint32_t)kAdjChunk ? ce - kAdjChunk : us;
+#pragma unroll
+        for (int i = 0; i < PARTS; i++) {
+            const int t = tid + i * NT;
+            rid[i] = t < 256 && cs + (uint32_t)(t >> 2) < ce ? vals[cs + (uint32_t)(t >> 2)] : ~0u;
+        }
+    };
+    auto fetch_recs = [&]() {
+#pragma unroll
+        for (int i = 0; i < PARTS; i++) {
+            const int part = (tid + i * NT) & 3;
+            kpre[i] = make_uint2(0u, 0u);
+            pre[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (rid[i] != ~0u) {
+                pre[i] = *sp.at(rid[i], part);
+                if (part == 0) kpre[i] = kp.rect[rid[i]];
+                else if (part == 1) kpre[i] = kp.rspan[rid[i]];
+                else if (part == 2) kpre[i].x = kp.koff[rid[i]];
+            }
+        }
+    };
+    if (top > us) {
+        fetch_ids(top);
+        fetch_recs();
+        const uint32_t cs = top - us > (uint32_t)kAdjChunk ? top - kAdjChunk : us;
+        if (cs > us) fetch_ids(cs);
+    }
+    int buf = 0;
+    for (uint32_t ce = top; ce > us; buf ^= 1) {
+        const uint32_t cs = ce - us > (uint32_t)kAdjChunk ? ce - (uint32_t)kAdjChunk : us;
+        const int nb = (int)(ce - cs);
+#pragma unroll
+        for (int i = 0; i < PARTS; i++) {
+            const int t = tid + i * NT;
+            if (t < 256) {
+                sh.rec[buf][t & 3][t >> 2] = pre[i];
+                if ((t & 3) < 3) sh.key[buf][t & 3][t >> 2] = kpre[i];
+            }
+        }
+        if (cs > us) {
+            fetch_recs();
+            const uint32_t ns = cs - us > (uint32_t)kAdjChunk ? cs - kAdjChunk : us;
+            if (ns > us) fetch_ids(ns);
+        }
+        __syncthreads();
+        const float4 *SA = sh.rec[buf][kRecA], *SB = sh.rec[buf][kRecB], *SC = sh.rec[buf][kRecC];
+        // the wave's splats of the chunk, back to front, as byte offsets from the
+        // first buffer's sections (whose starts are then the reads' constant offsets)
+        const int base = buf * (int)sizeof(sh.rec[0]);
+        const uint32_t off = cs - rg.x;   // list position of the chunk's first record
+        bool meet = lane < nb && off + (uint32_t)lane < qmax;
+        if (T > 8 && meet) {
+            const float4 e0 = sh.rec[buf][kRecEll][lane], a0 = SA[lane], c0 = SC[lane];
+            const Ellipse e{e0.x, e0.y, e0.z, e0.w, quad_half_height(e0), a0.x, a0.y, (int)c0.z, (int)c0.w};
+            meet = quad_meets(e, bx, by);
+        }
+        const uint64_t m64 = __ballot(meet);
+        const int cnt = (int)__popcll(m64);
+        int *const list = sh.list[wave];
+        if (meet) list[cnt - 1 - (int)lanes_below(m64)] = base + lane * (int)sizeof(float4);
+        if (lane < kAdjGroup) list[cnt + lane] = base + kAdjChunk * (int)sizeof(float4);
+        if (lane == 0) sh.hit[wave] = m64;
+        __builtin_amdgcn_wave_barrier();
+        // entries below the pixel's contributor count, as byte offsets
+        const int lim = base + (int)(nc - min(nc, off)) * (int)sizeof(float4);
+        for (int g = 0; g < cnt; g += kAdjGroup) {
+            uint32_t took = 0u;   // splats of the group that some pixel of the block included
+#pragma unroll
+            for (int h = 0; h < kAdjGroup; h += 4) {
+                if (g + h >= cnt) break;   // wave-uniform
+                const int4 j4 = *(const int4 *)(list + g + h);
+                const int bo[4] = {j4.x, j4.y, j4.z, j4.w};
+                // What does not depend on the recurrence, without branches.  A pixel
+                // the splat does not reach takes power -inf: exp2 = 0, alpha = 0,
+                // 1 / (1 - alpha) = 1, and its state passes through unchanged bit
+                // for bit with te = wT = 0.  A clamped alpha passes no gradient to
+                // the opacity or the power (exo = 0).
+                float al[4], inv[4], gc[4], exo[4], tb[4];
+                bool in4[4];
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    const float4 a = *(const float4 *)((const char *)sh.rec[0][kRecA] + bo[u]);
+                    const float4 b = *(const float4 *)((const char *)sh.rec[0][kRecB] + bo[u]);
+                    const float4 c = *(const float4 *)((const char *)sh.rec[0][kRecC] + bo[u]);
+                    const float dx = splat_dx(px, c.z, a.x);
+                    const float dy = splat_dx(py, c.w, a.y);
+                    const float power2 = splat_power2(a, b, dx, dy);
+                    const bool inc = (bo[u] < lim) & !(power2 > 0.f) & !(power2 < c.y);
+                    in4[u] = inc;
+                    if (__builtin_amdgcn_ballot_w64(inc)) took |= 1u << (h + u);
+                    const float ex = __builtin_amdgcn_exp2f(inc ? power2 : -__builtin_inff());
+                    const float ae = b.y * ex;
+                    al[u] = fminf(kAlphaMax, ae);
+                    inv[u] = __builtin_amdgcn_rcpf(1.f - al[u]);   // alpha <= 0.99
+                    gc[u] = fmaf(g2, c.x, fmaf(g1, b.w, g0 * b.z));
+                    exo[u] = ae > kAlphaMax ? 0.f : ex;
+                    if (MODE == 2)
+                        tb[u] = inc ? tstore[(size_t)(cs + (uint32_t)(bo[u] - base) / (uint32_t)sizeof(float4)) * (T * T) + pix]
+                                    : 0.f;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    const float Tb = MODE == 2 ? tb[u] : Tr * inv[u];
+                    const float dalpha = fmaf(Tb, gc[u], -(gR * inv[u]));
+                    const float wT = al[u] * Tb;
+                    gR = fmaf(gc[u], wT, gR);
+                    if (MODE != 2) Tr = Tb;
+                    row[(2 * (h + u)) * kAdjRow + lane] = MODE == 2 && !in4[u] ? 0.f : exo[u] * dalpha;
+                    row[(2 * (h + u) + 1) * kAdjRow + lane] = wT;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+            f32x4 D = {0.f, 0.f, 0.f, 0.f};
+            if (took) {
+                f32x4 av[4];
+#pragma unroll
+                for (int i = 0; i < 4; i++) av[i] = *(const f32x4 *)(row + (lane & 15) * kAdjRow + 16 * kq + 4 * i);
+#pragma unroll
+                for (int m = 0; m < 16; m++)
+                    D = __builtin_amdgcn_mfma_f32_16x16x4f32(av[m >> 2][m & 3], bq[m], D, 0, 0, 0);
+            }
+            // lane (j, k) holds column j of rows 4 k .. 4 k + 3: te and wT of the
+            // group's splats 2 k and 2 k + 1.  A splat no pixel included has zeros.
+            if (j < 9) {
+                const int2 jo = *(const int2 *)(list + g + 2 * kq);
+                const float s0 = j < 6 ? D[0] : D[1], s1 = j < 6 ? D[2] : D[3];
+                float *const S = sh.sum[wave] + j;
+                if (g + 2 * kq < cnt)
+                    S[((jo.x - base) >> 4) * 9] = (took >> (2 * kq)) & 1u ? s0 : 0.f;
+                if (g + 2 * kq + 1 < cnt)
+                    S[((jo.y - base) >> 4) * 9] = (took >> (2 * kq + 1)) & 1u ? s1 : 0.f;
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();
+        // The chunk's keys: thread (entry, piece) adds the blocks' sums about the
+        // splat's mean, applies the conic factors and stores its 16 bytes of the
+        // key's own 64-byte chunk (no other workgroup writes it):
+        //   dpower/dmean = (A dx + B dy, B dx + C dy) = -ln2 (2 A2 dx + B2 dy, B2 dx + 2 C2 dy);
+        //   dpower/d(A, B, C) = (-dx^2 / 2, -dx dy, -dy^2 / 2)
+#pragma unroll
+        for (int i = 0; i < PARTS; i++) {
+            const int t = tid + i * NT, e = t >> 2, part = t & 3;
+            if (t >= 256 || e >= nb) continue;
+            const float4 a = SA[e], b = SB[e], c = SC[e];
+            float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (part < 3) {
+                float sx = 0.f, sy = 0.f, sxx = 0.f, sxy = 0.f, syy = 0.f, s0 = 0.f, r0 = 0.f, r1 = 0.f, r2 = 0.f;
+#pragma unroll
+                for (int w = 0; w < NW; w++) {
+                    if (!((sh.hit[w] >> e) & 1ull)) continue;
+                    const float *M = sh.sum[w] + 9 * e;
+                    if (part == 2) {
+                        r2 += M[8];
+                        continue;
+                    }
+                    // the block centre's offset from the mean
+                    const float ey = splat_dx((float)(ty * T + (w / QX) * 8) + 3.5f, c.w, a.y);
+                    if (part == 1) {
+                        syy += fmaf(ey, fmaf(ey, M[0], 2.f * M[2]), M[5]);
+                        s0 += M[0];
+                        r0 += M[6];
+                        r1 += M[7];
+                        continue;
+                    }
+                    const float ex = splat_dx((float)(tx * T + (w % QX) * 8) + 3.5f, c.z, a.x);
+                    sx += fmaf(ex, M[0], M[1]);
+                    sy += fmaf(ey, M[0], M[2]);
+                    sxx += fmaf(ex, fmaf(ex, M[0], 2.f * M[1]), M[3]);
+                    sxy += fmaf(ex, fmaf(ey, M[0], M[2]), fmaf(ey, M[1], M[4]));
+                }
+                const float o = b.y;   // te sums -> dL/dpower sums
+                if (part == 0)
+                    out = make_float4(-kLn2 * o * (2.f * a.z * sx + a.w * sy),
+                                      -kLn2 * o * (a.w * sx + 2.f * b.x * sy), -0.5f * (o * sxx), -(o * sxy));
+                else if (part == 1)
+                    out = make_float4(-0.5f * (o * syy), s0, r0, r1);
+                else
+                    out.x = r2;
+            }
+            const uint32_t slot = key_slot_of(kp, sh.key[buf][0][e], sh.key[buf][1][e], sh.key[buf][2][e].x, ty, tx);
+            kp.pg[(size_t)slot * kKeyGradF4 + part] = out;
+        }
+        ce = cs;
+    }
+    // keys behind every pixel's last included splat pass no gradient
+    for (uint32_t t = (max(top, us) << 2) + (uint32_t)tid; (t >> 2) < ue; t += NT)
+        kp.pg[(size_t)key_slot(kp, vals[t >> 2], ty, tx) * kKeyGradF4 + (t & 3u)] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
+
+// ---- adjoint with one wave per tile, or per 16-pixel quarter of a 32-pixel tile ------
+//
+// Plans with many tiles are bound by VALU issue, so here one wave walks the
+// tile's list with (16 pixels and up) four pixels a lane (pixel block k = quadrant
+// k), sums its pixels' terms in the lane and reduces nine sums over the 64 lanes
+// once per splat.  That reduction is nine DPP adds (each row's lanes 8 apart, two fields
+// packed into a register by the bank masks), five 4-byte LDS stores, and, for
+// three splats at a time, 54 lanes that add half a row of 32 partial sums each:
+// about 60 VALU cycles a splat, where folding pairs of splats with permlane swaps
+// (8 cycles an instruction) and four DPP adds a row took 132.  An instruction
+// stream of 2-cycle operations (add, multiply, FMA) needs several waves ready on a
+// SIMD, so LDS (7 KB) and registers (82) are kept to five waves, and scalar
+// bookkeeping out of the loop.  Sixteen views of 1920^2, 16.7M keys: 2372 -> 1910
+// us; eight uneven views, 7.5M keys: 1100 -> 835 us.
+constexpr int kTileGroup = 3;              // splats whose partial sums are added together
+constexpr int kTileRow = 36;               // row stride of the 32 partial sums, floats
+// Opacities up to this cannot reach the alpha clamp (0.99; exp2 of a power <= 0
+// is at most 1 within rounding), so chunks without a larger one leave out the
+// clamp and its test (11 of about 112 VALU cycles per quadrant and splat).
+constexpr float kOpenOpacity = 0.98f;
+
+template <int T>
+constexpr int tile_adj_waves() { return T == 32 ? 4 : 1; }
+
+struct TileAdjWave {
+    // the chunk's records by section (a, b, c); a splat's nine sums replace its record
+    float4 rec[3][kAdjChunk];
+    alignas(16) float row[kTileGroup * 9 * kTileRow];
+};
+template <int T>
+struct TileAdjShared {
+    TileAdjWave wave[tile_adj_waves<T>()];
+    uint64_t hit[tile_adj_waves<T>()];   // splats of the chunk with sums (32-pixel tiles)
+    uint32_t nmax[tile_adj_waves<T>()];
+};
+
+// acc[f] summed over lanes 8 apart of each 16-lane row: fields 2 k (lanes 0-7 of
+// each row) and 2 k + 1 (lanes 8-15) in out[k], field 8 in out[4].  (The s_nop
+// gives the DPP reads the two wait states they need after the writes of acc.)
+__device__ __forceinline__ void fold8(const float (&acc)[9], float (&out)[5]) {
+    asm volatile(
+        "s_nop 1\n\t"
+        "v_add_f32_dpp %0, %5, %5 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %1, %7, %7 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %2, %9, %9 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %3, %11, %11 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %4, %13, %13 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %6, %6 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %1, %8, %8 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %2, %10, %10 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %3, %12, %12 row_ror:8 row_mask:0xf bank_mask:0xc"
+        : "=&v"(out[0]), "=&v"(out[1]), "=&v"(out[2]), "=&v"(out[3]), "=&v"(out[4])
+        : "v"(acc[0]), "v"(acc[1]), "v"(acc[2]), "v"(acc[3]), "v"(acc[4]), "v"(acc[5]), "v"(acc[6]),
+          "v"(acc[7]), "v"(acc[8]));
+}
+
+template <int T, int MODE>
+__device__ __forceinline__ void render_bwd_tile(
+    uint32_t ti, const TileMap &tm, uint32_t us, uint32_t ue, bool last_unit, const uint2 &rg,
+    uint32_t batch, const uint32_t *__restrict__ vals, SplatPtrs sp,
+    const ViewDesc *__restrict__ views, int nviews, const gsf_camera *__restrict__ cams,
+    const float *__restrict__ tfinal, const uint32_t *__restrict__ ncontrib,
+    const float4 *__restrict__ fstate, const float4 *__restrict__ ckpt,
+    const float *__restrict__ tstore, const float *__restrict__ bg, const float *__restrict__ dl,
+    const KeyPlace &kp, TileAdjShared<T> &shared) {
+    constexpr bool CKPT = MODE == 1;
+    constexpr int NW = tile_adj_waves<T>();
+    constexpr int PPT = T == 8 ? 1 : 4;
+    const int wave = NW > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) : 0;
+    TileAdjWave &sh = shared.wave[wave];
+    int v, ty, tx;
+    ViewDesc vd;
+    launch_tile(ti, tm, views, nviews, T, v, vd, ty, tx);   // a tile with keys: valid
+    const bool live = !tm.gaze || fovea_tile_live(tm.gaze, v, tm.radius, vd.width, vd.height, T, tx, ty);
+    const float disk_r = tm.gaze ? tm.radius * (float)vd.width : 0.f;
     const int lane = threadIdx.x & 63;
     const float *bgv = bg ? bg + 3 * v : cams[v].bg;
     const float bg0 = bgv[0], bg1 = bgv[1], bg2 = bgv[2];
     const size_t plane = (size_t)vd.width * vd.height;
     const float *dimg = dl + 4 * (size_t)vd.pix_off;
 
-    // gR: dL/dC-weighted colour behind the current splat, less gA Tf (the alpha
-    // plane's share), carried as one value since only that difference is used
+    // the pixel state, as render_bwd_unit has it, for the lane's pixel of each quadrant
     float px[PPT], py[PPT], Tr[PPT], Tf[PPT], gR[PPT], g0[PPT], g1[PPT], g2[PPT], gA[PPT];
-    uint32_t nc[PPT];
-    int pix[PPT];   // the pixel's row-major index in the tile
-    uint32_t my_max = 0;
+    uint32_t nc[PPT], qmax[PPT];
+    int pix[PPT];
 #pragma unroll
     for (int k = 0; k < PPT; k++) {
-        const int lx = QUAD ? (k & 1) * 8 + (lane & 7) : threadIdx.x % T;
-        const int ly = QUAD ? (k >> 1) * 8 + (lane >> 3) : threadIdx.x / T + k * ROWS;
+        const int lx = (wave & 1) * 16 + (k & 1) * 8 + (lane & 7);
+        const int ly = (wave >> 1) * 16 + (k >> 1) * 8 + (lane >> 3);
         pix[k] = ly * T + lx;
         const int x = tx * T + lx, y = ty * T + ly;
         const bool inside = live && x < vd.width && y < vd.height && in_fovea(tm.gaze, v, x, y, disk_r);
         const size_t q = inside ? (size_t)y * vd.width + x : 0;
-        px[k] = (float)x;   // integer pixel; its centre's offset from a mean is splat_dx
+        px[k] = (float)x;
         py[k] = (float)y;
+        nc[k] = 0u;
         if (inside) {
             Tf[k] = tfinal[vd.pix_off + q];
             nc[k] = ncontrib[vd.pix_off + q];
@@ -573,129 +894,115 @@ __device__ __forceinline__ void render_bwd_unit(
             g2[k] = dimg[2 * plane + q];
             gA[k] = dimg[3 * plane + q];
         }
-        // a pixel no splat reached passes no gradient, whatever its dL/dimage
-        // (which a fovea-culled loss may not have written): it starts at zero
-        if (!inside || nc[k] == 0u) {
+        if (nc[k] == 0u) {
             Tf[k] = 1.f;
-            nc[k] = 0u;
             g0[k] = g1[k] = g2[k] = gA[k] = 0.f;
         }
-        const float gbg = Tf[k] * (g0[k] * bg0 + g1[k] * bg1 + g2[k] * bg2);
+        gR[k] = Tf[k] * (g0[k] * bg0 + g1[k] * bg1 + g2[k] * bg2);
+        Tr[k] = Tf[k];
         if (CKPT && !last_unit && rg.x + nc[k] > us) {
-            // colour behind the unit = final colour - colour accumulated at its end
             const float4 fs = fstate[vd.pix_off + q];
-            const float4 cp = ckpt[(size_t)(ue / B) * (T * T) + pix[k]];
+            const float4 cp = ckpt[(size_t)(ue / batch) * (T * T) + pix[k]];
             Tr[k] = cp.x;
-            gR[k] = gbg + g0[k] * (fs.y - cp.y) + g1[k] * (fs.z - cp.z) + g2[k] * (fs.w - cp.w);
-        } else {
-            Tr[k] = Tf[k];
-            gR[k] = gbg;
+            gR[k] = gR[k] + g0[k] * (fs.y - cp.y) + g1[k] * (fs.z - cp.z) + g2[k] * (fs.w - cp.w);
         }
         gR[k] -= gA[k] * Tf[k];
-        my_max = max(my_max, nc[k]);
     }
-    // 16-pixel tiles: per quadrant (one per pixel block of the wave) the largest
-    // contributor count; a splat at or past it reaches no pixel of the quadrant
-    // (each would add exact zeros and keep its state), so the quadrant is skipped
-    uint32_t qmax[PPT];
+    // per quadrant the largest contributor count: a splat at or past it reaches no
+    // pixel of the quadrant
+    uint32_t nmax = 0u;
 #pragma unroll
     for (int k = 0; k < PPT; k++) {
         uint32_t x = nc[k];
-        if (QUAD) {
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) x = max(x, (uint32_t)__shfl_xor((int)x, o, 64));
-            x = __builtin_amdgcn_readfirstlane(x);
-        }
-        qmax[k] = x;
+        for (int o = 32; o > 0; o >>= 1) x = max(x, (uint32_t)__shfl_xor((int)x, o, 64));
+        qmax[k] = __builtin_amdgcn_readfirstlane(x);
+        nmax = max(nmax, qmax[k]);
     }
-    // the tile's largest contributor count: a wave reduction, then (several
-    // waves) their maximum through LDS (an LDS atomic with per-lane values
-    // would be serialised over the lanes)
-    uint32_t nmax;
-    if (QUAD) {
-        nmax = max(max(qmax[0], qmax[1]), max(qmax[2], qmax[3]));
-    } else {
+    if constexpr (NW > 1) {   // the tile's
+        if (lane == 0) shared.nmax[wave] = nmax;
+        __syncthreads();
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) my_max = max(my_max, (uint32_t)__shfl_xor((int)my_max, o, 64));
-        nmax = __builtin_amdgcn_readfirstlane(my_max);
-        if (NW > 1) {
-            __syncthreads();
-            if (lane == 0) s_nmax[threadIdx.x >> 6] = nmax;
-            __syncthreads();
-#pragma unroll
-            for (int w = 0; w < NW; w++) nmax = max(nmax, s_nmax[w]);
-        }
+        for (int w = 0; w < NW; w++) nmax = max(nmax, shared.nmax[w]);
     }
     const uint32_t top = min(ue, rg.x + nmax);
+    // the lane's row of partial sums (splat lane / 18, field lane / 2 % 9), its
+    // half, and where in the splat's record that field's sum goes
+    const int prow = lane >> 1, psplat = prow / 9, pfield = prow - 9 * psplat;
+    const int prd = prow * kTileRow + (lane & 1) * 4;
+    const int psum = (pfield >> 2) * (4 * kAdjChunk) + (pfield & 3);
+    const int pwr = ((lane >> 3) & 1) * kTileRow + (lane >> 4) * 8 + (lane & 7);
 
+    uint32_t rid = 0u;   // record ids are read a chunk ahead
+    if (top > us) {
+        const uint32_t cs = top - us > (uint32_t)kAdjChunk ? top - kAdjChunk : us;
+        if (cs + (uint32_t)lane < top) rid = vals[cs + (uint32_t)lane];
+    }
     for (uint32_t be = top; be > us;) {
-        const uint32_t bs = be - us > (uint32_t)B ? be - (uint32_t)B : us;
+        const uint32_t bs = be - us > (uint32_t)kAdjChunk ? be - (uint32_t)kAdjChunk : us;
         const int nb = (int)(be - bs);
-        __syncthreads();
-        for (int j = threadIdx.x; j < nb; j += NT) {
-            const uint32_t r = vals[bs + j];
-            const float4 *rr = sp.at(r, 0);   // one 64-byte chunk: splat and ellipse
+        const uint32_t off = bs - rg.x;   // list position of the chunk's first record
+        // the lane's record: conic factors, opacity, its key's slot and the
+        // quadrants it reaches before their deepest contributor
+        float A2 = 0.f, B2 = 0.f, C2 = 0.f, o = 0.f;
+        uint32_t slot = 0u, qmask = 0u;
+        if (lane < nb) {
+            const float4 *rr = sp.at(rid, 0);   // one 64-byte chunk: splat and ellipse
             const float4 ra = rr[kRecA], rb = rr[kRecB], rc = rr[kRecC], e0 = rr[kRecEll];
-            s_a[j] = ra;
-            s_b[j] = rb;
-            s_c[j] = rc;
-            s_q[j] = key_slot(kp, r, ty, tx);
-            if (QUAD) {
+            if (wave == 0) slot = key_slot(kp, rid, ty, tx);
+            sh.rec[0][lane] = ra;
+            sh.rec[1][lane] = rb;
+            sh.rec[2][lane] = rc;
+            A2 = ra.z;
+            B2 = ra.w;
+            C2 = rb.x;
+            o = rb.y;
+            if constexpr (T >= 16) {
                 const Ellipse e{e0.x, e0.y, e0.z, e0.w, quad_half_height(e0), ra.x, ra.y, (int)rc.z, (int)rc.w};
-                s_m[j] = (uint8_t)quadrant_mask(e, tx * T, ty * T);
+                qmask = quadrant_mask(e, tx * T + (wave & 1) * 16, ty * T + (wave >> 1) * 16);
             } else {
-                s_h[j] = support_half_height(e0);
+                qmask = 1u;   // the list holds the splats that reach the tile's one block
             }
+#pragma unroll
+            for (int k = 0; k < PPT; k++)
+                if (off + (uint32_t)lane >= qmax[k]) qmask &= ~(1u << k);
         }
-        __syncthreads();
-        uint64_t hit = 0ull;   // splats of the current block of R some pixel of the wave took
+        if (bs > us) {
+            const uint32_t ns = bs - us > (uint32_t)kAdjChunk ? bs - kAdjChunk : us;
+            if (ns + (uint32_t)lane < bs) rid = vals[ns + (uint32_t)lane];
+        }
+        __builtin_amdgcn_wave_barrier();
         // Splat j's per-lane sums: te dx, te dy, te dx^2, te dx dy, te dy^2 (te =
-        // dL/do, so that o te = dL/dpower), dL/do, dL/dcolour; the opacity and
-        // the conic factors of the mean gradient are applied once per splat when
-        // the sums are flushed.  True if some pixel of the wave took the splat.
-        auto splat_terms = [&](int j, float (&acc)[9]) -> bool {
-            const uint32_t pos = bs + (uint32_t)j - rg.x;   // list position in the tile
-            const float4 a = s_a[j];
-            const float4 b = s_b[j];
-            const float4 c = s_c[j];
-            const float hy = QUAD ? 0.f : s_h[j];
+        // dL/do, so that o te = dL/dpower), dL/do, dL/dcolour; folded into group
+        // row G.
+        auto splat = [&](int j, int G, auto clamp_tag) __attribute__((always_inline)) {
+            constexpr bool CLAMP = decltype(clamp_tag)::value;
+            const uint32_t pos = off + (uint32_t)j;
+            const float4 a = sh.rec[0][j], b = sh.rec[1][j], c = sh.rec[2][j];
             // the splat's quadrant mask, wave-uniform: tested in scalar registers
-            const uint32_t qm = QUAD ? __builtin_amdgcn_readfirstlane((uint32_t)s_m[j]) : 0u;
-            // row offset of the tile's first row from the mean; block k adds k ROWS
-            const float dy0 = splat_dx((float)(ty * T), c.w, a.y);
+            const uint32_t qm = (uint32_t)__builtin_amdgcn_readlane((int)qmask, j);
+            float acc[9];
             // (-0 is the exact identity of addition, so the first term needs no add)
 #pragma unroll
             for (int f = 0; f < 9; f++) acc[f] = -0.f;
-            // some pixel of the wave took the splat: with quadrants, known
-            // (wave-uniform) from the quadrant skip; else from a per-lane flag
-            bool took = false, any = false;
 #pragma unroll
             for (int k = 0; k < PPT; k++) {
-                if (QUAD ? (!((qm >> k) & 1u) || pos >= qmax[k])                     // wave-uniform
-                         : !rows_meet(dy0 + (float)(k * ROWS), (float)(ROWS - 1), hy)) continue;
+                if (!((qm >> k) & 1u)) continue;   // wave-uniform
                 // Branch-free per lane: every value is computed and a pixel the
                 // splat does not reach (behind its last contributor, or alpha
-                // below 1/255) adds exact zeros and keeps its state.  An
-                // included pixel does exactly the float operations of the adjoint.
+                // below 1/255) takes power -inf instead, so exp2 = 0, alpha = 0, 1 /
+                // (1 - alpha) = 1 and its state passes through unchanged bit for bit
+                // with zero sums, without a select per quantity.
                 const float dx = splat_dx(px[k], c.z, a.x);
                 const float dy = splat_dx(py[k], c.w, a.y);
                 const float power2 = splat_power2(a, b, dx, dy);
                 const bool inc = (pos < nc[k]) & !(power2 > 0.f) & !(power2 < c.y);
                 // no pixel of the block takes the splat: every lane would add
                 // zeros and keep its state (wave-uniform)
-                if (QUAD) {
-                    if (!__any(inc)) continue;
-                    took = true;
-                } else {
-                    any |= inc;
-                }
-                // Recomputed transmittance: a pixel the splat does not reach
-                // takes power -inf instead, so exp2 = 0, alpha = 0, 1 / (1 - alpha)
-                // = 1 and its state passes through unchanged bit for bit (Tr x 1,
-                // gR + gc x 0) with zero sums, without a select per quantity.
+                if (!__any(inc)) continue;
                 const float ex = __builtin_amdgcn_exp2f(MODE == 2 || inc ? power2 : -__builtin_inff());
                 const float ae = b.y * ex;
-                const float alpha = fminf(kAlphaMax, ae);
+                const float alpha = CLAMP ? fminf(kAlphaMax, ae) : ae;
                 const float inv = __builtin_amdgcn_rcpf(1.f - alpha);   // alpha <= 0.99
                 float Tb;
                 if (MODE == 2)
@@ -714,8 +1021,8 @@ __device__ __forceinline__ void render_bwd_unit(
                 // a clamped alpha passes no gradient to the opacity or the power;
                 // te = dL/do, and dL/dpower (natural units) = o te, the opacity
                 // factor being applied to the sums once per splat at the flush
-                const bool open = (MODE != 2 || inc) & !(ae > kAlphaMax);
-                const float te = open ? ex * dalpha : 0.f;
+                float te = ex * dalpha;
+                if (CLAMP || MODE == 2) te = ((MODE != 2 || inc) & !(ae > kAlphaMax)) ? te : 0.f;
                 acc[5] += te;
                 const float ux = te * dx, uy = te * dy;
                 acc[0] += ux;
@@ -724,160 +1031,155 @@ __device__ __forceinline__ void render_bwd_unit(
                 acc[3] = fmaf(ux, dy, acc[3]);
                 acc[4] = fmaf(uy, dy, acc[4]);
             }
-            return QUAD ? took : __any(any);
-        };
-        // Wave sums of the pair of splats (j + 1, j), j even, at once
-        // (pair_sums); the row leaders store them into the wave's slots, and the
-        // wave notes the splats some pixel took in its hit mask (a splat none
-        // took is read as zero).
-        auto store_pair = [&](int j, const float (&accA)[9], bool hitA, const float (&acc)[9],
-                              bool hitj) {
-            if (!(hitA || hitj)) return;
             float out[5];
-            pair_sums(accA, acc, out);
-            const int lane = __lane_id();
-            if ((lane & 15) == 15) {
-                const int row = lane >> 4, par = row & 1;
-                const int js = row < 2 ? j + 1 : j;
-                float *g = s_g + (threadIdx.x >> 6) * GS + (js & (R - 1)) * 9 + par;
-                g[0] = out[0];
-                g[2] = out[1];
-                g[4] = out[2];
-                g[6] = out[3];
-                if (!par) g[8] = out[4];
-            }
-            if (hitA) hit |= 1ull << ((j + 1) & (R - 1));
-            if (hitj) hit |= 1ull << (j & (R - 1));
+            fold8(acc, out);
+            const int w = pwr + G * (9 * kTileRow);
+#pragma unroll
+            for (int k = 0; k < 4; k++) sh.row[w + 2 * k * kTileRow] = out[k];
+            if (!(lane & 8)) sh.row[w + 8 * kTileRow] = out[4];
         };
-        // after splat j (even): at a multiple of R, splats j .. j + R - 1 are
-        // done: one lane per splat adds the waves' sums, applies the conic
-        // factors and stores them at the key's own position (no other workgroup
-        // writes it)
-        auto flush = [&](int j) {
-            if ((j & (R - 1)) != 0) return;
-            if (NW > 1) {
-                if (__lane_id() == 0) s_hit[threadIdx.x >> 6] = hit;
-                __syncthreads();
-            }
-            const int t = (int)threadIdx.x, jj = j + t;
-            if (t < R && jj < nb) {
-                float S[9];
+        // The splats that reach some quadrant, back to front, kTileGroup at a time;
+        // then the group's rows are added: a lane adds half a row, its neighbour
+        // the other half.
+        const uint64_t some = __builtin_amdgcn_ballot_w64(qmask != 0u);
+        auto walk = [&](auto clamp_tag) __attribute__((always_inline)) {
+            uint64_t m = some;
+            while (m) {   // wave-uniform
+                int id[kTileGroup];
 #pragma unroll
-                for (int f = 0; f < 9; f++) S[f] = 0.f;
-#pragma unroll
-                for (int w = 0; w < NW; w++) {
-                    const uint64_t hw = NW > 1 ? s_hit[w] : hit;
-                    if (!((hw >> t) & 1ull)) continue;
-#pragma unroll
-                    for (int f = 0; f < 9; f++) S[f] += s_g[w * GS + t * 9 + f];
+                for (int G = 0; G < kTileGroup; G++) {
+                    id[G] = -1;
+                    if (m) {
+                        id[G] = 63 - __builtin_clzll(m);
+                        m &= ~(1ull << id[G]);
+                        splat(id[G], G, clamp_tag);
+                    }
                 }
-                const float A2 = s_a[jj].z, B2 = s_a[jj].w, C2 = s_b[jj].x, o = s_b[jj].y;
-                const uint32_t q = s_q[jj];
+                __builtin_amdgcn_wave_barrier();
+                int mine = -1;   // the lane's splat (none past the group's last)
 #pragma unroll
-                for (int f = 0; f < 5; f++) S[f] *= o;   // te sums -> dL/dpower sums
-                // dpower/dmean = (A dx + B dy, B dx + C dy) = -ln2 (2 A2 dx + B2 dy, B2 dx + 2 C2 dy);
-                // dpower/d(A, B, C) = (-dx^2 / 2, -dx dy, -dy^2 / 2)
-                float4 *g = kp.pg + (size_t)q * kKeyGradF4;
-                g[0] = make_float4(-kLn2 * (2.f * A2 * S[0] + B2 * S[1]),
-                                   -kLn2 * (B2 * S[0] + 2.f * C2 * S[1]), -0.5f * S[2], -S[3]);
-                g[1] = make_float4(-0.5f * S[4], S[5], S[6], S[7]);
-                g[2] = make_float4(S[8], 0.f, 0.f, 0.f);
-                g[3] = make_float4(0.f, 0.f, 0.f, 0.f);
+                for (int G = 0; G < kTileGroup; G++) mine = psplat == G ? id[G] : mine;
+                if (mine >= 0) {
+                    float4 x[4];
+#pragma unroll
+                    for (int i = 0; i < 4; i++) x[i] = *(const float4 *)(sh.row + prd + 8 * i);
+                    const float s0 = (x[0].x + x[0].y) + (x[0].z + x[0].w), s1 = (x[1].x + x[1].y) + (x[1].z + x[1].w);
+                    const float s2 = (x[2].x + x[2].y) + (x[2].z + x[2].w), s3 = (x[3].x + x[3].y) + (x[3].z + x[3].w);
+                    float t = (s0 + s1) + (s2 + s3);
+                    t += dpp_shift<0xB1, 0xf>(t);   // quad_perm [1, 0, 3, 2]: the other half
+                    if (!(lane & 1)) ((float *)sh.rec)[4 * mine + psum] = t;
+                }
+                __builtin_amdgcn_wave_barrier();
             }
-            if (NW > 1) __syncthreads();   // the slots are free again
-            hit = 0ull;
         };
-        // back to front by pairs (2 g + 1, 2 g), both splats' sums in registers
-        // of their own; with an odd count the top splat (even) pairs with zeros
-        int j = nb - 1;
-        if (!(j & 1)) {
-            float accA[9], acc[9];
+        if (__builtin_amdgcn_ballot_w64(o > kOpenOpacity)) walk(std::true_type{});
+        else walk(std::false_type{});
+        if constexpr (NW > 1) {
+            if (lane == 0) shared.hit[wave] = some;
+            __syncthreads();
+        }
+        // one lane per splat adds the waves' nine sums, applies the conic factors and
+        // stores them at the key's own position (no other workgroup writes it)
+        if (wave == 0 && lane < nb) {
+            float S[9];
 #pragma unroll
-            for (int f = 0; f < 9; f++) accA[f] = -0.f;
-            const bool hitj = splat_terms(j, acc);
-            store_pair(j, accA, false, acc, hitj);
-            flush(j);
-            j--;
+            for (int f = 0; f < 9; f++) S[f] = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; w++) {
+                if (!(((NW > 1 ? shared.hit[w] : some) >> lane) & 1ull)) continue;
+#pragma unroll
+                for (int f = 0; f < 9; f++)
+                    S[f] += ((const float *)shared.wave[w].rec)[4 * lane + (f >> 2) * (4 * kAdjChunk) + (f & 3)];
+            }
+#pragma unroll
+            for (int f = 0; f < 5; f++) S[f] *= o;   // te sums -> dL/dpower sums
+            // dpower/dmean = (A dx + B dy, B dx + C dy) = -ln2 (2 A2 dx + B2 dy, B2 dx + 2 C2 dy);
+            // dpower/d(A, B, C) = (-dx^2 / 2, -dx dy, -dy^2 / 2)
+            float4 *g = kp.pg + (size_t)slot * kKeyGradF4;
+            g[0] = make_float4(-kLn2 * (2.f * A2 * S[0] + B2 * S[1]),
+                               -kLn2 * (B2 * S[0] + 2.f * C2 * S[1]), -0.5f * S[2], -S[3]);
+            g[1] = make_float4(-0.5f * S[4], S[5], S[6], S[7]);
+            g[2] = make_float4(S[8], 0.f, 0.f, 0.f);
+            g[3] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        for (; j > 0; j -= 2) {
-            float accA[9], acc[9];
-            const bool hitA = splat_terms(j, accA);
-            const bool hitj = splat_terms(j - 1, acc);
-            store_pair(j - 1, accA, hitA, acc, hitj);
-            flush(j - 1);
-        }
+        if constexpr (NW > 1) __syncthreads();   // the chunk's LDS is free again
+        else __builtin_amdgcn_wave_barrier();
         be = bs;
     }
     // keys behind every pixel's last included splat pass no gradient
-    for (uint32_t e = max(top, us) + threadIdx.x; e < ue; e += NT) {
-        const uint32_t q = key_slot(kp, vals[e], ty, tx);
-        float4 *g = kp.pg + (size_t)q * kKeyGradF4;
+    for (uint32_t e = max(top, us) + threadIdx.x; e < ue; e += 64u * NW) {
+        float4 *g = kp.pg + (size_t)key_slot(kp, vals[e], ty, tx) * kKeyGradF4;
 #pragma unroll
         for (int f = 0; f < kKeyGradF4; f++) g[f] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
 }
 
+// WIDE: one wave per 8 x 8 block (render_bwd_unit); else one wave per tile or
+// quarter tile (render_bwd_tile).
+template <int T, bool WIDE>
+struct AdjForm {
+    using Shared = AdjShared<T>;
+};
+template <int T>
+struct AdjForm<T, false> {
+    using Shared = TileAdjShared<T>;
+};
+template <int T, bool WIDE>
+constexpr int adj_threads() { return 64 * (WIDE ? adj_waves<T>() : tile_adj_waves<T>()); }
+
 // Recompute (MODE 0) and stored (MODE 2) modes: one workgroup per tile, the
 // whole list back to front; workgroup i takes tile order[i] like the forward.
-template <int T, int B, int MODE>
-__global__ __launch_bounds__(bwd_threads<T>()) void k_render_bwd(
+template <int T, int MODE, bool WIDE>
+__global__ __launch_bounds__((adj_threads<T, WIDE>()), WIDE && T == 16 ? 4 : 1) void k_render_bwd(
     const uint32_t *__restrict__ order,
     const uint2 *__restrict__ ranges, const uint32_t *__restrict__ vals, SplatPtrs sp,
     const ViewDesc *__restrict__ views, int nviews, const gsf_camera *__restrict__ cams,
     const float *__restrict__ tfinal, const uint32_t *__restrict__ ncontrib,
     const float *__restrict__ tstore, const float *__restrict__ bg, const float *__restrict__ dl,
     KeyPlace kp, TileMap tm) {
-    constexpr int NT = bwd_threads<T>();
-    __shared__ float4 s_a[B];
-    __shared__ float4 s_b[B];
-    __shared__ float4 s_c[B];
-    __shared__ uint32_t s_q[B];
-    __shared__ uint8_t s_m[B];
-    __shared__ float s_g[NT / 64 * kGradSlot<MODE>];
-    __shared__ uint64_t s_hit[NT / 64];
-    __shared__ float s_h[B];
-    __shared__ uint32_t s_nmax[NT / 64];
+    __shared__ typename AdjForm<T, WIDE>::Shared sh;
     const uint32_t ti = order[blockIdx.x];
     const uint2 rg = ranges[ti];
     // a tile without keys passes no gradient (and a fovea-culled step's tiles
     // away from the fovea hold no pixel state to read)
     if (rg.x == rg.y) return;
-    render_bwd_unit<T, B, MODE>(ti, tm, rg.x, rg.y, true, rg, vals, sp, views, nviews, cams, tfinal,
-                                ncontrib, nullptr, nullptr, tstore, bg, dl, kp, s_a, s_b, s_c, s_q,
-                                s_m, s_g, s_hit, s_h, s_nmax);
+    if constexpr (WIDE)
+        render_bwd_unit<T, MODE>(ti, tm, rg.x, rg.y, true, rg, 1u, vals, sp, views, nviews, cams, tfinal,
+                                 ncontrib, nullptr, nullptr, tstore, bg, dl, kp, sh);
+    else
+        render_bwd_tile<T, MODE>(ti, tm, rg.x, rg.y, true, rg, 1u, vals, sp, views, nviews, cams, tfinal,
+                              ncontrib, nullptr, nullptr, tstore, bg, dl, kp, sh);
 }
 
 // Checkpoint mode: one workgroup per (tile, batch) unit id.  Unit u of tile t
 // has id floor(start_t / B) + t + u (strictly increasing, below M / B + tiles);
-// a workgroup maps its id back to its tile by binary search.  The grid covers
+// a workgroup maps its id back to its tile by a 64-way search (each wave's lanes
+// test 64 tiles at once: two rounds of loads for 4,096 tiles where halving takes
+// twelve).  The grid covers
 // the key capacity; ids at or above M / B + tiles (M read on the device) and
 // ids that fall in no tile's units exit at once.
-template <int T, int B>
-__global__ __launch_bounds__(bwd_threads<T>()) void k_render_bwd_ckpt(
-    const uint2 *__restrict__ ranges, int total_tiles, const uint32_t *__restrict__ m_dev,
+template <int T, bool WIDE>
+__global__ __launch_bounds__((adj_threads<T, WIDE>()), WIDE && T == 16 ? 4 : 1) void k_render_bwd_ckpt(
+    const uint2 *__restrict__ ranges, int total_tiles, uint32_t B, const uint32_t *__restrict__ m_dev,
     uint32_t m_host, const uint32_t *__restrict__ vals, SplatPtrs sp,
     const ViewDesc *__restrict__ views, int nviews, const gsf_camera *__restrict__ cams,
     const float *__restrict__ tfinal, const uint32_t *__restrict__ ncontrib,
     const float4 *__restrict__ fstate, const float4 *__restrict__ ckpt,
     const float *__restrict__ bg, const float *__restrict__ dl, KeyPlace kp, TileMap tm) {
-    constexpr int NT = bwd_threads<T>();
-    __shared__ float4 s_a[B];
-    __shared__ float4 s_b[B];
-    __shared__ float4 s_c[B];
-    __shared__ uint32_t s_q[B];
-    __shared__ uint8_t s_m[B];
-    __shared__ float s_g[NT / 64 * kGradSlot<1>];
-    __shared__ uint64_t s_hit[NT / 64];
-    __shared__ float s_h[B];
-    __shared__ uint32_t s_nmax[NT / 64];
+    __shared__ typename AdjForm<T, WIDE>::Shared sh;
     const uint32_t m = m_dev ? *m_dev : m_host;
     const uint32_t n_ids = m / B + (uint32_t)total_tiles;
+    const int lane = (int)(threadIdx.x & 63);
     for (uint32_t id = blockIdx.x; id < n_ids; id += gridDim.x) {   // one trip when the grid covers n_ids
-        // largest tile t with first id floor(start_t / B) + t <= id
-        int lo = 0, hi = total_tiles - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (ranges[mid].x / B + (uint32_t)mid <= id) lo = mid; else hi = mid - 1;
+        // largest tile t with first id floor(start_t / B) + t <= id: in [lo, lo + len)
+        int lo = 0, len = total_tiles;
+        while (len > 1) {   // wave-uniform
+            const int step = (len + 63) >> 6, t = lo + lane * step;
+            const bool le = lane * step < len && ranges[t].x / B + (uint32_t)t <= id;
+            // monotone in t, and true for lo: the last true lane
+            const int k = 63 - __builtin_clzll(__ballot(le) | 1ull);
+            len = min(step, len - k * step);
+            lo += k * step;
         }
         const uint2 rg = ranges[lo];
         const uint32_t u = id - (rg.x / B + (uint32_t)lo);
@@ -885,9 +1187,13 @@ __global__ __launch_bounds__(bwd_threads<T>()) void k_render_bwd_ckpt(
         if (u >= units) continue;
         const uint32_t us = rg.x + u * B;
         const uint32_t ue = min(rg.y, us + B);
-        render_bwd_unit<T, B, 1>((uint32_t)lo, tm, us, ue, u + 1 == units, rg, vals, sp, views, nviews, cams,
-                                 tfinal, ncontrib, fstate, ckpt, nullptr, bg, dl, kp, s_a, s_b,
-                                 s_c, s_q, s_m, s_g, s_hit, s_h, s_nmax);
+        if constexpr (WIDE)
+            render_bwd_unit<T, 1>((uint32_t)lo, tm, us, ue, u + 1 == units, rg, B, vals, sp, views, nviews,
+                                  cams, tfinal, ncontrib, fstate, ckpt, nullptr, bg, dl, kp, sh);
+        else
+            render_bwd_tile<T, 1>((uint32_t)lo, tm, us, ue, u + 1 == units, rg, B, vals, sp, views, nviews,
+                               cams, tfinal, ncontrib, fstate, ckpt, nullptr, bg, dl, kp, sh);
+        __syncthreads();   // the unit's LDS is free again
     }
 }
 
@@ -1310,22 +1616,21 @@ void render_fwd_tb(hipStream_t s, const RenderArgs &a, float *out) {
         render_fwd_tbs<T, B, false>(s, a, out);
 }
 
-template <int T, int B>
-void render_bwd_tb(hipStream_t s, const RenderArgs &a, const float *dl) {
-    constexpr int NT = bwd_threads<T>();
+template <int T, bool WIDE>
+void render_bwd_tw(hipStream_t s, const RenderArgs &a, const float *dl) {
+    constexpr int NT = adj_threads<T, WIDE>();
     if (a.t_mode == 1)
-        k_render_bwd_ckpt<T, B><<<a.bwd_grid, NT, 0, s>>>(a.ranges, a.total_tiles, a.m_dev, a.m_host,
-                                                         a.vals, a.sp, a.views, a.nviews, a.cams,
-                                                         a.tfinal, a.ncontrib, a.fstate, a.ckpt, a.bg,
-                                                         dl, a.kp, a.tm);
+        k_render_bwd_ckpt<T, WIDE><<<a.bwd_grid, NT, 0, s>>>(
+            a.ranges, a.total_tiles, (uint32_t)a.batch, a.m_dev, a.m_host, a.vals, a.sp, a.views, a.nviews,
+            a.cams, a.tfinal, a.ncontrib, a.fstate, a.ckpt, a.bg, dl, a.kp, a.tm);
     else if (a.t_mode == 2)
-        k_render_bwd<T, B, 2><<<a.total_tiles, NT, 0, s>>>(a.order, a.ranges, a.vals, a.sp,
-                                                        a.views, a.nviews, a.cams, a.tfinal,
-                                                        a.ncontrib, a.tstore, a.bg, dl, a.kp, a.tm);
+        k_render_bwd<T, 2, WIDE><<<a.total_tiles, NT, 0, s>>>(a.order, a.ranges, a.vals, a.sp, a.views,
+                                                             a.nviews, a.cams, a.tfinal, a.ncontrib,
+                                                             a.tstore, a.bg, dl, a.kp, a.tm);
     else
-        k_render_bwd<T, B, 0><<<a.total_tiles, NT, 0, s>>>(a.order, a.ranges, a.vals, a.sp,
-                                                        a.views, a.nviews, a.cams, a.tfinal,
-                                                        a.ncontrib, nullptr, a.bg, dl, a.kp, a.tm);
+        k_render_bwd<T, 0, WIDE><<<a.total_tiles, NT, 0, s>>>(a.order, a.ranges, a.vals, a.sp, a.views,
+                                                             a.nviews, a.cams, a.tfinal, a.ncontrib,
+                                                             nullptr, a.bg, dl, a.kp, a.tm);
 }
 
 template <int T>
@@ -1335,11 +1640,23 @@ void render_fwd_t(hipStream_t s, const RenderArgs &a, float *out) {
     else render_fwd_tb<T, 256>(s, a, out);
 }
 
+// The adjoint takes one wave per 8 x 8 block while the plan has at most
+// kWideTilesPerCu (checkpointed mode, whose units cut the lists short:
+// kWideCkptTilesPerCu) 16-pixel tiles' worth of tiles per compute unit, one wave per
+// tile above.  Checkpointed, one 512^2 view (1,024 tiles) 40 against 64 us, three
+// views of 0.17-0.48 Mpix (3,800 tiles) 212 against 147, one of 1024^2 (4,096) 107
+// against 80; recomputed, 701 x 533 (1,496) 72 against 153, the three views 537
+// against 1086, 8-pixel tiles on 1024^2 175 against 219, eight views of 0.25-4 Mpix
+// (42,000) 1399 against 835.
+constexpr int kWideTilesPerCu = 16, kWideCkptTilesPerCu = 8;
+
 template <int T>
 void render_bwd_t(hipStream_t s, const RenderArgs &a, const float *dl) {
-    if (a.batch == 64) render_bwd_tb<T, 64>(s, a, dl);
-    else if (a.batch == 128) render_bwd_tb<T, 128>(s, a, dl);
-    else render_bwd_tb<T, 256>(s, a, dl);
+    const int per_cu = a.t_mode == 1 ? kWideCkptTilesPerCu : kWideTilesPerCu;
+    if ((int64_t)a.total_tiles * (T * T) <= (int64_t)per_cu * 256 * a.cus)
+        render_bwd_tw<T, true>(s, a, dl);
+    else
+        render_bwd_tw<T, false>(s, a, dl);
 }
 
 }  // namespace
