@@ -634,7 +634,7 @@ hipError_t run_first_hits(hipStream_t s, const uint16_t *vol, int n, const gsf_c
                           float extinction, float thr, float range, const float *lo, const float *hi,
                           float hit_alpha, int color_steps, double opacity, int64_t cap,
                           uint64_t seed, float *params, int64_t *count, int32_t *ray_ids,
-                          void *scratch);
+                          void *scratch, void *occ);
 
 // Seeding from a device volume (synchronises); scratch: seed_scratch_bytes(n^3).
 hipError_t run_seed(hipStream_t s, const uint16_t *vol, int n, double thr, double range,
@@ -645,7 +645,10 @@ size_t seed_scratch_bytes(int64_t nvox);
 hipError_t run_raymarch(hipStream_t s, const uint16_t *vol, int n, const gsf_camera *cams, int nviews,
                         const int32_t *widths, const int32_t *heights, float step, float extinction,
                         float t_stop, float thr, float range, const float *lo, const float *hi,
-                        float *out);
+                        float *out, void *occ);
+// Device bytes of the occupancy grid both marches build in `occ` and skip empty
+// space by (null: they sample every segment).
+size_t occupancy_bytes();
 
 void launch_fill_u32(hipStream_t s, uint32_t *p, int64_t n, uint32_t value);
 void launch_fill_f32(hipStream_t s, float *p, int64_t n, float value);

@@ -33,6 +33,12 @@ struct gsf_ctx {
     std::string err;
     unsigned long long *warp_scratch = nullptr;   // device address of the no-allocation z-buffer
     hipError_t warp_scratch_err = hipSuccess;
+    // small device scratch of the calls that read a volume (volume_scratch): the
+    // stream it was last used on, and the event that use ended with
+    void *vol_scratch = nullptr;
+    hipEvent_t vol_event = nullptr;
+    hipStream_t vol_stream = nullptr;
+    bool vol_used = false;
 };
 
 namespace {
@@ -150,6 +156,53 @@ gsf_status fail(gsf_ctx *ctx, gsf_status st, const std::string &msg) {
         if (e_ != hipSuccess)                                                                \
             return fail((ctx), GSF_E_HIP, std::string("kernel launch: ") + hipGetErrorString(e_)); \
     } while (0)
+
+// Whether the stream is being captured (or cannot say so).
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+}
+
+// The context's volume scratch (occupancy_bytes()), for work about to be enqueued on
+// its stream; the work of an earlier call on another stream is waited for first.
+// Null under capture, where the graph could run beside a later call: the marches then
+// skip nothing.  volume_scratch_done follows the work.
+void *volume_scratch(gsf_ctx *ctx) {
+    if (capturing(ctx->stream)) return nullptr;
+    if (!ctx->vol_scratch) {
+        // (relaxed: a capture that is under way on another stream goes on)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return nullptr;
+        void *p = nullptr;
+        hipEvent_t e = nullptr;
+        bool ok = hipMalloc(&p, occupancy_bytes()) == hipSuccess;
+        if (ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+            (void)hipFree(p);
+            ok = false;
+        }
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (!ok) {
+            (void)hipGetLastError();   // the march goes on without
+            return nullptr;
+        }
+        ctx->vol_scratch = p;
+        ctx->vol_event = e;
+    }
+    if (ctx->vol_used && ctx->vol_stream != ctx->stream &&
+        hipStreamWaitEvent(ctx->stream, ctx->vol_event, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    return ctx->vol_scratch;
+}
+
+gsf_status volume_scratch_done(gsf_ctx *ctx, const void *scratch) {
+    if (!scratch) return GSF_OK;
+    ctx->vol_stream = ctx->stream;
+    ctx->vol_used = true;
+    GSF_HIP(ctx, hipEventRecord(ctx->vol_event, ctx->stream));
+    return GSF_OK;
+}
 
 int planes_of(int deg) { return 11 + 3 * (deg + 1) * (deg + 1); }
 
@@ -590,11 +643,19 @@ gsf_status gsf_ctx_create(int device, void *hip_stream, gsf_ctx **out) {
         c->cus = cus;
     // the no-allocation warp's z-buffer: its address on this device, found once
     c->warp_scratch_err = warp_scratch_address(device, &c->warp_scratch);
+    (void)volume_scratch(c);   // allocated here rather than in the first march
     *out = c;
     return GSF_OK;
 }
 
 gsf_status gsf_ctx_destroy(gsf_ctx *ctx) {
+    if (ctx && ctx->vol_scratch) {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;   // as in volume_scratch
+        const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        (void)hipFree(ctx->vol_scratch);   // waits for the work that uses it
+        (void)hipEventDestroy(ctx->vol_event);
+        if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
     delete ctx;
     return GSF_OK;
 }
@@ -833,9 +894,10 @@ gsf_status gsf_raymarch(gsf_ctx *ctx, const uint16_t *vol, int32_t n, const gsf_
             return fail(ctx, GSF_E_INVALID, "gsf_raymarch: image size out of range");
     if (!(step > 0.f) || !(range > 0.f) || !(t_stop >= 0.f) || !(extinction >= 0.f))
         return fail(ctx, GSF_E_INVALID, "gsf_raymarch: step, range, extinction or t_stop invalid");
+    void *occ = volume_scratch(ctx);
     GSF_HIP(ctx, run_raymarch(ctx->stream, vol, n, cams, n_views, widths, heights, step, extinction,
-                              t_stop, threshold, range, lo, hi, out_rgba));
-    return GSF_OK;
+                              t_stop, threshold, range, lo, hi, out_rgba, occ));
+    return volume_scratch_done(ctx, occ);
 }
 
 gsf_status gsf_adam(gsf_ctx *ctx, float *prm, const float *g, float *m, float *v, int64_t n_elems,
@@ -921,10 +983,11 @@ gsf_status gsf_seed_first_hits(gsf_ctx *ctx, const uint16_t *vol, int32_t n, con
         return fail(ctx, GSF_E_INVALID, "gsf_seed_first_hits: scratch too small");
     if (((uintptr_t)scratch & 255u) != 0)
         return fail(ctx, GSF_E_INVALID, "gsf_seed_first_hits: scratch must be 256-byte aligned");
+    void *occ = volume_scratch(ctx);
     GSF_HIP(ctx, run_first_hits(ctx->stream, vol, n, cams, n_views, widths, heights, step,
                                 extinction, threshold, range, lo, hi, hit_alpha, color_steps,
-                                opacity, cap, seed, params, count, ray_ids, scratch));
-    return GSF_OK;
+                                opacity, cap, seed, params, count, ray_ids, scratch, occ));
+    return volume_scratch_done(ctx, occ);
 }
 
 gsf_status gsf_reproject(gsf_ctx *ctx, const float *depth, int32_t width, int32_t height,
