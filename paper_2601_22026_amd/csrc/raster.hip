@@ -24,11 +24,13 @@
 // units, each rebuilding T within its batch) and stored (the forward stores
 // T_i of every included (splat, pixel) pair at [key position][pixel of tile];
 // the adjoint reads it; one workgroup per tile).  The nine per-splat screen-space
-// gradient terms of a wave are summed across its lanes with DPP row
-// operations, kept per row in LDS, and stored once per (key, field) at the
-// key's own position; a separate pass sums each record's keys (no atomics).
-// With 16-pixel tiles each wave covers an 8x8 quadrant of the tile and skips
-// the splats whose padded support ellipse misses it.
+// gradient terms are summed over a tile's pixels and stored once per (key, field)
+// at the key's own position; a separate pass sums each record's keys (no atomics).
+// Two forms of the adjoint: for plans of few tiles one wave per 8x8 block, which sums
+// the terms of eight splats with matrix products (more waves than tiles); for many
+// tiles one wave per tile, which folds them with DPP adds and LDS rows (fewer vector
+// cycles).  Where a wave covers an 8x8 quadrant of a 16-pixel tile it skips the splats
+// whose padded support ellipse misses it.
 #include <type_traits>
 
 #include "gs_internal.h"
