@@ -625,6 +625,15 @@ void launch_reproject_warp(hipStream_t s, const ReprojConstOpaque &k, const floa
                            const float *depth, int out_w, int out_h, unsigned long long *zbuf,
                            float *out_rgba, int32_t *src);
 
+// Scratch of the calls that read a volume: the marches' grid of occupied cells (they
+// read every segment without) and the seeding's selection; device:
+// volume_scratch_bytes(), host: two pinned words that the device writes.
+struct VolumeScratch {
+    void *device = nullptr;
+    unsigned long long *host = nullptr;
+};
+size_t volume_scratch_bytes();
+
 // First-hit point cloud (synchronises): Gaussians at the first significant hit
 // of every pixel ray of the cameras, capped by ray priority; scratch:
 // first_hit_scratch_bytes(total rays).
@@ -634,21 +643,18 @@ hipError_t run_first_hits(hipStream_t s, const uint16_t *vol, int n, const gsf_c
                           float extinction, float thr, float range, const float *lo, const float *hi,
                           float hit_alpha, int color_steps, double opacity, int64_t cap,
                           uint64_t seed, float *params, int64_t *count, int32_t *ray_ids,
-                          void *scratch, void *occ);
+                          void *scratch, const VolumeScratch &vs, int cus);
 
 // Seeding from a device volume (synchronises); scratch: seed_scratch_bytes(n^3).
 hipError_t run_seed(hipStream_t s, const uint16_t *vol, int n, double thr, double range,
                     const double *lo, const double *hi, double opacity, int64_t cap, uint64_t seed,
-                    float *params, int64_t *count, void *scratch);
+                    float *params, int64_t *count, void *scratch, const VolumeScratch &vs, int cus);
 size_t seed_scratch_bytes(int64_t nvox);
 // Emission-absorption targets of n_views cameras (asynchronous).
 hipError_t run_raymarch(hipStream_t s, const uint16_t *vol, int n, const gsf_camera *cams, int nviews,
                         const int32_t *widths, const int32_t *heights, float step, float extinction,
                         float t_stop, float thr, float range, const float *lo, const float *hi,
-                        float *out, void *occ);
-// Device bytes of the occupancy grid both marches build in `occ` and skip empty
-// space by (null: they sample every segment).
-size_t occupancy_bytes();
+                        float *out, const VolumeScratch &vs);
 
 void launch_fill_u32(hipStream_t s, uint32_t *p, int64_t n, uint32_t value);
 void launch_fill_f32(hipStream_t s, float *p, int64_t n, float value);

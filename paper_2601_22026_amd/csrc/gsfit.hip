@@ -35,7 +35,7 @@ struct gsf_ctx {
     hipError_t warp_scratch_err = hipSuccess;
     // small device scratch of the calls that read a volume (volume_scratch): the
     // stream it was last used on, and the event that use ended with
-    void *vol_scratch = nullptr;
+    VolumeScratch vol_scratch;
     hipEvent_t vol_event = nullptr;
     hipStream_t vol_stream = nullptr;
     bool vol_used = false;
@@ -163,41 +163,43 @@ bool capturing(hipStream_t s) {
     return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
 }
 
-// The context's volume scratch (occupancy_bytes()), for work about to be enqueued on
-// its stream; the work of an earlier call on another stream is waited for first.
-// Null under capture, where the graph could run beside a later call: the marches then
-// skip nothing.  volume_scratch_done follows the work.
-void *volume_scratch(gsf_ctx *ctx) {
-    if (capturing(ctx->stream)) return nullptr;
-    if (!ctx->vol_scratch) {
+// The context's volume scratch, for work about to be enqueued on its stream; the work
+// of an earlier call on another stream is waited for first.  Empty under capture,
+// where the graph could run beside a later call: a march then skips nothing (and the
+// seeding, which synchronises, is refused).  volume_scratch_done follows the work.
+VolumeScratch volume_scratch(gsf_ctx *ctx) {
+    if (capturing(ctx->stream)) return {};
+    if (!ctx->vol_scratch.device) {
         // (relaxed: a capture that is under way on another stream goes on)
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return nullptr;
-        void *p = nullptr;
+        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return {};
+        void *p = nullptr, *h = nullptr;
         hipEvent_t e = nullptr;
-        bool ok = hipMalloc(&p, occupancy_bytes()) == hipSuccess;
-        if (ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-            (void)hipFree(p);
-            ok = false;
+        const bool ok = hipMalloc(&p, volume_scratch_bytes()) == hipSuccess &&
+                        hipHostMalloc(&h, 2 * sizeof(unsigned long long)) == hipSuccess &&
+                        hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+        if (!ok) {
+            if (p) (void)hipFree(p);
+            if (h) (void)hipHostFree(h);
         }
         (void)hipThreadExchangeStreamCaptureMode(&mode);
         if (!ok) {
-            (void)hipGetLastError();   // the march goes on without
-            return nullptr;
+            (void)hipGetLastError();   // a march goes on without
+            return {};
         }
-        ctx->vol_scratch = p;
+        ctx->vol_scratch = {p, (unsigned long long *)h};
         ctx->vol_event = e;
     }
     if (ctx->vol_used && ctx->vol_stream != ctx->stream &&
         hipStreamWaitEvent(ctx->stream, ctx->vol_event, 0) != hipSuccess) {
         (void)hipGetLastError();
-        return nullptr;
+        return {};
     }
     return ctx->vol_scratch;
 }
 
-gsf_status volume_scratch_done(gsf_ctx *ctx, const void *scratch) {
-    if (!scratch) return GSF_OK;
+gsf_status volume_scratch_done(gsf_ctx *ctx, const VolumeScratch &vs) {
+    if (!vs.device) return GSF_OK;
     ctx->vol_stream = ctx->stream;
     ctx->vol_used = true;
     GSF_HIP(ctx, hipEventRecord(ctx->vol_event, ctx->stream));
@@ -649,10 +651,11 @@ gsf_status gsf_ctx_create(int device, void *hip_stream, gsf_ctx **out) {
 }
 
 gsf_status gsf_ctx_destroy(gsf_ctx *ctx) {
-    if (ctx && ctx->vol_scratch) {
+    if (ctx && ctx->vol_scratch.device) {
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;   // as in volume_scratch
         const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-        (void)hipFree(ctx->vol_scratch);   // waits for the work that uses it
+        (void)hipFree(ctx->vol_scratch.device);   // waits for the work that uses it
+        (void)hipHostFree(ctx->vol_scratch.host);
         (void)hipEventDestroy(ctx->vol_event);
         if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
@@ -875,9 +878,10 @@ gsf_status gsf_seed_volume(gsf_ctx *ctx, const uint16_t *vol, int32_t n, double 
     if (!(opacity > 0.0 && opacity < 1.0)) return fail(ctx, GSF_E_INVALID, "gsf_seed_volume: opacity must lie in (0, 1)");
     if (scratch_bytes < seed_scratch_bytes((int64_t)n * n * n))
         return fail(ctx, GSF_E_INVALID, "gsf_seed_volume: scratch too small");
+    const VolumeScratch vs = volume_scratch(ctx);
     GSF_HIP(ctx, run_seed(ctx->stream, vol, n, threshold, range, lo, hi, opacity, cap, seed, params,
-                          count, scratch));
-    return GSF_OK;
+                          count, scratch, vs, ctx->cus));
+    return volume_scratch_done(ctx, vs);
 }
 
 gsf_status gsf_raymarch(gsf_ctx *ctx, const uint16_t *vol, int32_t n, const gsf_camera *cams,
@@ -894,10 +898,10 @@ gsf_status gsf_raymarch(gsf_ctx *ctx, const uint16_t *vol, int32_t n, const gsf_
             return fail(ctx, GSF_E_INVALID, "gsf_raymarch: image size out of range");
     if (!(step > 0.f) || !(range > 0.f) || !(t_stop >= 0.f) || !(extinction >= 0.f))
         return fail(ctx, GSF_E_INVALID, "gsf_raymarch: step, range, extinction or t_stop invalid");
-    void *occ = volume_scratch(ctx);
+    const VolumeScratch vs = volume_scratch(ctx);
     GSF_HIP(ctx, run_raymarch(ctx->stream, vol, n, cams, n_views, widths, heights, step, extinction,
-                              t_stop, threshold, range, lo, hi, out_rgba, occ));
-    return volume_scratch_done(ctx, occ);
+                              t_stop, threshold, range, lo, hi, out_rgba, vs));
+    return volume_scratch_done(ctx, vs);
 }
 
 gsf_status gsf_adam(gsf_ctx *ctx, float *prm, const float *g, float *m, float *v, int64_t n_elems,
@@ -983,11 +987,11 @@ gsf_status gsf_seed_first_hits(gsf_ctx *ctx, const uint16_t *vol, int32_t n, con
         return fail(ctx, GSF_E_INVALID, "gsf_seed_first_hits: scratch too small");
     if (((uintptr_t)scratch & 255u) != 0)
         return fail(ctx, GSF_E_INVALID, "gsf_seed_first_hits: scratch must be 256-byte aligned");
-    void *occ = volume_scratch(ctx);
+    const VolumeScratch vs = volume_scratch(ctx);
     GSF_HIP(ctx, run_first_hits(ctx->stream, vol, n, cams, n_views, widths, heights, step,
                                 extinction, threshold, range, lo, hi, hit_alpha, color_steps,
-                                opacity, cap, seed, params, count, ray_ids, scratch, occ));
-    return volume_scratch_done(ctx, occ);
+                                opacity, cap, seed, params, count, ray_ids, scratch, vs, ctx->cus));
+    return volume_scratch_done(ctx, vs);
 }
 
 gsf_status gsf_reproject(gsf_ctx *ctx, const float *depth, int32_t width, int32_t height,

@@ -10,11 +10,11 @@
 // raster order.  Priority of voxel idx: the SplitMix64 output idx + 1 from
 // state seed with its low b bits replaced by idx (b = bits of n^3 - 1), so
 // priorities are distinct and the kept set is a uniform random subset.  The
-// cap-th smallest priority is found by an MSB-first radix select (eight 8-bit
-// digit histograms), then the kept voxels are written in raster order.  Mean =
-// voxel centre, isotropic log-scale, identity rotation, the given opacity and
-// the transfer-function colour as degree-0 SH, in double precision rounded
-// once to float.
+// cap-th smallest priority is found on the device (digit histograms, then the few
+// candidates that share its first digits), and the kept voxels are written in
+// raster order.  Mean = voxel centre, isotropic log-scale, identity rotation, the
+// given opacity and the transfer-function colour as degree-0 SH, in double precision
+// rounded once to float.  The first hits of rays are capped the same way.
 //
 // Ray march: one ray per pixel, emission-absorption through the box
 // [-1, 1]^3 in float32 - segments of the step length from the box entry (the
@@ -22,8 +22,8 @@
 // each segment's midpoint, density t = clamp((v - thr) / range, 0, 1), colour
 // lerp(lo, hi, t), alpha = 1 - exp(-extinction t length), stop once T < t_stop;
 // RGB = C + T bg, A = 1 - T.
+#include <algorithm>
 #include <cmath>
-#include <vector>
 
 #include "gs_internal.h"
 
@@ -31,8 +31,14 @@ namespace gsf {
 namespace {
 
 constexpr int kVolBlock = 256;
-constexpr int kVolIpt = 8;                       // voxels per thread per block
-constexpr int kVolTile = kVolBlock * kVolIpt;
+constexpr int kItemLane = 8;                          // consecutive items of a thread
+constexpr int kItemWave = 64 * kItemLane;             // items of a wave
+constexpr int kItemTile = 4 * kItemWave;              // items counted and placed together
+constexpr int kSelBlock = 1024;                       // threads that histogram and collect
+constexpr int kSelList = 512;                         // undecided keys that a workgroup gathers
+constexpr int kDigitBits = 10, kDigits = 1 << kDigitBits;
+constexpr int kMaxLevels = 6;                         // 60 bits settled: 16 keys at most share them
+constexpr int kUndecided = 4096;                      // keys that share the settled digits, at most
 
 __device__ __forceinline__ uint64_t splitmix64(uint64_t state, uint64_t k) {
     uint64_t z = state + k * 0x9E3779B97F4A7C15ull;
@@ -45,107 +51,426 @@ __device__ __forceinline__ uint64_t priority(uint64_t seed, uint64_t idx, int ib
     return ((splitmix64(seed, idx + 1ull) >> ibits) << ibits) | idx;
 }
 
-// Digit histogram of the candidates whose priority agrees with `prefix` on the
-// bits above `shift + 8`; 256 bins accumulated per workgroup in LDS.
-__global__ __launch_bounds__(kVolBlock) void k_seed_hist(const uint16_t *__restrict__ vol, int64_t nvox,
-                                                         float thr, uint64_t seed, int ibits,
-                                                         uint64_t prefix, int shift,
-                                                         unsigned long long *__restrict__ hist) {
-    __shared__ uint32_t h[256];
-    h[threadIdx.x] = 0u;
+// ---- selection of the cap smallest priorities ----------------------------------------
+// Items 0 .. n - 1 (voxels, or rays), some of them candidates.  On the device, without
+// the host in between:
+//   a histogram of the candidates' priorities by their leading 10 bits, and by 10 more
+//   within those that it settles, until few enough share them (a further one returns at
+//   once where that is so already, as with 2 million candidates of 256^3 voxels);
+//   per tile of 2048 items the candidates that are kept for certain, and a list of the
+//   undecided;
+//   the list resolved, and the tiles' offsets, by one workgroup;
+//   the kept items written at their places.
+// The list overflows only where priorities crowd: the host sees it after its one
+// synchronisation and asks for one digit more.
+// The two passes that count read 4 x 16 bytes a lane before they look at any: 20 and 27
+// us for 256^3 voxels, of which the 64-bit products of the priorities take about 10 and
+// the memory 7 (one load waited for at a time: 24 and 28; workgroups of 256 threads, 8
+// a CU, with their 2 million adds to the histogram in memory: 43 and 33; one digit of
+// 12 bits: 42 and 27; two of 8 bits: 43 and 21).  Writing: 27 us, resolving 15.
+// 500000 voxels of 256^3: 501 us before (eight 8-bit histograms by scalar loads, the
+// host waiting for each, and the offsets summed there), 117 now.  20000 first hits of
+// 8 x 256 x 256 rays: 473 us before, 278 now.
+
+struct Selection {
+    unsigned long long hist[kMaxLevels][kDigits];
+    unsigned long long list[kUndecided];
+    unsigned long long kstar, kept;   // the largest kept priority; how many are kept
+    uint32_t listed, overflow;
+};
+
+struct SelArgs {
+    int64_t n, cap;
+    uint64_t seed;
+    int ibits, tiles;
+    Selection *sel;
+    uint32_t *counts;   // per tile: certainly kept, then the offset of its first kept item
+};
+
+// Candidate voxels: those of at least `least`.
+struct VoxelItems {
+    const uint16_t *vol;
+    uint32_t least;
+    bool wide;   // 16-byte aligned
+    // Bit k: item i + k is a candidate (i a multiple of 8).
+    __device__ __forceinline__ uint32_t mask8(int64_t i, int64_t n) const {
+        uint32_t m = 0u;
+        if (i >= n) return 0u;
+        if (wide && i + kItemLane <= n) {
+            const uint4 q = *reinterpret_cast<const uint4 *>(vol + i);
+            const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                m |= (w[k] & 0xFFFFu) >= least ? 1u << (2 * k) : 0u;
+                m |= (w[k] >> 16) >= least ? 2u << (2 * k) : 0u;
+            }
+            return m;
+        }
+#pragma unroll
+        for (int k = 0; k < kItemLane; k++)
+            if (i + k < n) m |= (uint32_t)vol[i + k] >= least ? 1u << k : 0u;
+        return m;
+    }
+};
+
+// Candidate rays: those that hit (bytes 0 and 1, room for a multiple of 8 of them).
+struct RayItems {
+    const uint8_t *hit;
+    __device__ __forceinline__ uint32_t mask8(int64_t i, int64_t n) const {
+        if (i >= n) return 0u;
+        const uint2 q = *reinterpret_cast<const uint2 *>(hit + i);
+        uint32_t m = 0u;
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            m |= (q.x >> (8 * k) & 1u) << k;
+            m |= (q.y >> (8 * k) & 1u) << (4 + k);
+        }
+        return i + kItemLane <= n ? m : m & ((1u << (int)(n - i)) - 1u);
+    }
+};
+
+__global__ __launch_bounds__(kVolBlock) void k_select_clear(SelArgs a, int levels) {
+    const int i = blockIdx.x * kVolBlock + threadIdx.x;
+    if (i < levels * kDigits) (&a.sel->hist[0][0])[i] = 0ull;
+    if (i < a.tiles) a.counts[i] = 0u;
+    if (i == 0) {
+        a.sel->listed = 0u;
+        a.sel->overflow = 0u;
+    }
+}
+
+// Inclusive sum of x over the workgroup's threads up to this one, and the total.
+template <int BLOCK, class T>
+__device__ __forceinline__ T block_scan(T x, T &total) {
+    __shared__ T s_sum[BLOCK / 64];
+    const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const T y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    __syncthreads();   // the sums of an earlier scan have been read
+    if (lane == 63) s_sum[w] = x;
     __syncthreads();
-    const uint64_t hi_mask = shift + 8 >= 64 ? 0ull : ~0ull << (shift + 8);
-    for (int64_t i = (int64_t)blockIdx.x * kVolBlock + threadIdx.x; i < nvox;
-         i += (int64_t)gridDim.x * kVolBlock) {
-        if (!((float)vol[i] > thr)) continue;
-        const uint64_t key = priority(seed, (uint64_t)i, ibits);
-        if ((key & hi_mask) != (prefix & hi_mask)) continue;
-        atomicAdd(&h[(key >> shift) & 255u], 1u);
+    total = 0;
+#pragma unroll
+    for (int k = 0; k < BLOCK / 64; k++) {
+        if (k < w) x += s_sum[k];
+        total += s_sum[k];
+    }
+    return x;
+}
+
+struct Pick {
+    uint64_t prefix;   // the settled digits of the cap-th smallest priority
+    int64_t rank;      // its 1-based rank among the candidates that share them
+    int levels;        // how many digits are settled
+    bool all;          // every candidate is kept
+    bool few;          // or those that share the digits fit the list
+};
+
+// The digit in which the histogram's running sum reaches rank, which drops by the sum
+// before it; its count, and the histogram's total.  Called by every thread of the
+// workgroup.
+template <int BLOCK, class T>
+__device__ __forceinline__ int find_digit(const T *hist, int64_t &rank, int64_t &count, int64_t &total) {
+    constexpr int kPer = kDigits / BLOCK;
+    __shared__ int s_digit;
+    __shared__ int64_t s_rank, s_count;
+    unsigned long long own = 0ull, sum;
+#pragma unroll
+    for (int k = 0; k < kPer; k++) own += hist[threadIdx.x * kPer + k];
+    int64_t before = (int64_t)(block_scan<BLOCK>(own, sum) - own);
+    total = (int64_t)sum;
+    const int64_t want = rank < total ? rank : total;
+    if (before < want && before + (int64_t)own >= want) {
+        int k = 0;
+        int64_t h;
+        for (; before + (h = (int64_t)hist[threadIdx.x * kPer + k]) < want; k++) before += h;
+        s_digit = (int)threadIdx.x * kPer + k;
+        s_rank = rank - before;
+        s_count = h;
     }
     __syncthreads();
-    if (h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], (unsigned long long)h[threadIdx.x]);
-}
-
-__device__ __forceinline__ bool kept(const uint16_t *__restrict__ vol, int64_t i, float thr,
-                                     uint64_t seed, int ibits, uint64_t kstar) {
-    return (float)vol[i] > thr && priority(seed, (uint64_t)i, ibits) <= kstar;
-}
-
-// Kept voxels per block of kVolTile voxels.
-__global__ __launch_bounds__(kVolBlock) void k_seed_count(const uint16_t *__restrict__ vol, int64_t nvox,
-                                                          float thr, uint64_t seed, int ibits,
-                                                          uint64_t kstar, uint32_t *__restrict__ counts) {
-    __shared__ uint32_t s_cnt;
-    if (threadIdx.x == 0) s_cnt = 0u;
+    const int d = total ? s_digit : 0;
+    count = total ? s_count : 0;
+    if (total) rank = s_rank;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kVolTile + (int64_t)threadIdx.x * kVolIpt;
-    uint32_t c = 0;
+    return d;
+}
+
+__device__ __forceinline__ int digit_shift(int level) { return 64 - kDigitBits * (level + 1); }
+
+template <int BLOCK>
+__device__ __forceinline__ Pick pick(const SelArgs &a, int levels) {
+    Pick p{0ull, a.cap, 0, false, false};
+    while (p.levels < levels && !p.all && !p.few) {
+        int64_t count, total;
+        const int d = find_digit<BLOCK>(a.sel->hist[p.levels], p.rank, count, total);
+        p.all = p.levels == 0 && total <= a.cap;
+        p.few = count <= kUndecided;
+        p.prefix |= (uint64_t)d << digit_shift(p.levels++);
+    }
+    return p;
+}
+
+// Calls f(k, priority) for each of the thread's candidates first + k.
+template <class F>
+__device__ __forceinline__ void for_keys(uint32_t mask, int64_t first, const SelArgs &a, F f) {
 #pragma unroll
-    for (int k = 0; k < kVolIpt; k++)
-        if (base + k < nvox && kept(vol, base + k, thr, seed, ibits, kstar)) c++;
-    if (c) atomicAdd(&s_cnt, c);
-    __syncthreads();
-    if (threadIdx.x == 0) counts[blockIdx.x] = s_cnt;
+    for (int k = 0; k < kItemLane; k++)
+        if (mask >> k & 1u) f(k, priority(a.seed, (uint64_t)(first + k), a.ibits));
 }
 
-struct SeedConst {
+// Calls f(tile, first item, candidates) for each wave's 512 items, four of them read
+// at a time, far apart as candidates cluster.
+template <class ITEMS, class F>
+__device__ __forceinline__ void for_waves(const ITEMS &items, const SelArgs &a, F f) {
+    const int64_t waves = 4 * (int64_t)a.tiles, stride = (int64_t)gridDim.x * (kSelBlock / 64);
+    for (int64_t c = (int64_t)blockIdx.x * (kSelBlock / 64) + (threadIdx.x >> 6); c < waves; c += 4 * stride) {
+        const int64_t lane0 = (threadIdx.x & 63) * kItemLane;
+        uint32_t m[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) m[q] = items.mask8((c + q * stride) * kItemWave + lane0, a.n);
+#pragma unroll 1
+        for (int q = 0; q < 4; q++) {
+            const uint32_t mq = q == 0 ? m[0] : (q == 1 ? m[1] : (q == 2 ? m[2] : m[3]));
+            if (__builtin_amdgcn_ballot_w64(mq != 0u) == 0ull) continue;
+            f((int)((c + q * stride) >> 2), (c + q * stride) * kItemWave + lane0, mq);
+        }
+    }
+}
+
+// Histogram of the digit after `level` settled ones.
+template <class ITEMS>
+__global__ __launch_bounds__(kSelBlock) void k_select_hist(ITEMS items, SelArgs a, int level) {
+    __shared__ uint32_t h[kDigits];
+    Pick p{};
+    if (level) {
+        p = pick<kSelBlock>(a, level);
+        if (p.all || p.few) return;
+    }
+    for (int d = threadIdx.x; d < kDigits; d += kSelBlock) h[d] = 0u;
+    __syncthreads();
+    const int shift = digit_shift(level);
+    for_waves(items, a, [&](int, int64_t first, uint32_t m) {
+        for_keys(m, first, a, [&](int, uint64_t key) {
+            if (level == 0 || ((key ^ p.prefix) >> (shift + kDigitBits)) == 0ull)
+                atomicAdd(&h[(key >> shift) & (kDigits - 1)], 1u);
+        });
+    });
+    __syncthreads();
+    for (int d = threadIdx.x; d < kDigits; d += kSelBlock)
+        if (h[d]) atomicAdd(&a.sel->hist[level][d], (unsigned long long)h[d]);
+}
+
+// Per tile the candidates that are kept for certain: those whose settled digits are
+// below the cap-th's, or all of them.  Those that share its digits go to the list.
+template <class ITEMS>
+__global__ __launch_bounds__(kSelBlock) void k_select_collect(ITEMS items, SelArgs a, int levels) {
+    __shared__ unsigned long long s_key[kSelList];
+    __shared__ uint32_t s_listed, s_at;
+    if (threadIdx.x == 0) s_listed = 0u;
+    const Pick p = pick<kSelBlock>(a, levels);
+    __syncthreads();
+    const int shift = digit_shift(p.levels - 1);
+    const uint64_t want = p.prefix >> shift;
+    for_waves(items, a, [&](int t, int64_t first, uint32_t m) {
+        uint32_t c = 0u;
+        if (p.all) c = __popc(m);
+        else
+            for_keys(m, first, a, [&](int, uint64_t key) {
+                const uint64_t top = key >> shift;
+                c += top < want ? 1u : 0u;
+                if (top != want) return;
+                uint32_t at = atomicAdd(&s_listed, 1u);
+                if (at < kSelList) {
+                    s_key[at] = key;
+                    return;
+                }
+                at = atomicAdd(&a.sel->listed, 1u);
+                if (at < kUndecided) a.sel->list[at] = key;
+            });
+#pragma unroll
+        for (int o = 32; o; o >>= 1) c += __shfl_xor(c, o, 64);
+        if ((threadIdx.x & 63) == 0 && c) atomicAdd(&a.counts[t], c);
+    });
+    __syncthreads();
+    const uint32_t n = min(s_listed, (uint32_t)kSelList);
+    if (threadIdx.x == 0 && n) s_at = atomicAdd(&a.sel->listed, n);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n; i += kSelBlock)
+        if (s_at + i < kUndecided) a.sel->list[s_at + i] = s_key[i];
+}
+
+// One workgroup: the largest kept priority from the list, its kept keys counted in
+// their tiles, and the tiles' counts turned into offsets.  host: {kept, overflow}.
+__global__ __launch_bounds__(1024) void k_select_finish(SelArgs a, int levels, unsigned long long *host) {
+    __shared__ unsigned long long s_key[kUndecided];
+    constexpr int kTiles = 4096;
+    __shared__ uint32_t s_hist[kTiles];   // a digit's; then of 4096 tiles at a time, the list's kept keys
+    const int t = (int)threadIdx.x;
+    const Pick p = pick<1024>(a, levels);
+    const uint32_t listed = p.all ? 0u : a.sel->listed;
+    if (listed > kUndecided) {
+        if (t == 0) {
+            a.sel->overflow = 1u;
+            host[0] = 0ull;
+            host[1] = 1ull;
+        }
+        return;
+    }
+    uint64_t kstar = ~0ull;
+    if (!p.all) {
+        for (uint32_t i = t; i < listed; i += 1024) s_key[i] = a.sel->list[i];
+        uint64_t prefix = p.prefix, settled = ~0ull << digit_shift(p.levels - 1);
+        int64_t rank = p.rank;
+        for (int level = p.levels; ~settled; level++) {
+            const int shift = max(digit_shift(level), 0);   // (the last digit takes settled bits along)
+            for (int d = t; d < kDigits; d += 1024) s_hist[d] = 0u;
+            __syncthreads();
+            for (uint32_t i = t; i < listed; i += 1024)
+                if (((s_key[i] ^ prefix) & settled) == 0ull)
+                    atomicAdd(&s_hist[(s_key[i] >> shift) & (kDigits - 1)], 1u);
+            __syncthreads();
+            int64_t count, total;
+            const int d = find_digit<1024>(s_hist, rank, count, total);
+            prefix |= (uint64_t)d << shift;
+            settled |= (uint64_t)(kDigits - 1) << shift;
+            if (count == rank) break;   // all that share the digits are kept
+        }
+        kstar = prefix | ~settled;
+    }
+    const uint64_t imask = (1ull << a.ibits) - 1ull;
+    uint32_t sum = 0u;
+    for (int base = 0; base < a.tiles; base += kTiles) {
+        for (int k = t; k < kTiles; k += 1024) s_hist[k] = 0u;
+        __syncthreads();
+        for (uint32_t i = t; i < listed; i += 1024) {
+            const int64_t tile = (int64_t)((s_key[i] & imask) / kItemTile) - base;
+            if (s_key[i] <= kstar && tile >= 0 && tile < kTiles) atomicAdd(&s_hist[tile], 1u);
+        }
+        __syncthreads();
+        const int first = base + t * 4;
+        uint32_t c[4], own = 0u, total;
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            c[k] = first + k < a.tiles ? a.counts[first + k] + s_hist[t * 4 + k] : 0u;
+            own += c[k];
+        }
+        uint32_t at = sum + block_scan<1024>(own, total) - own;
+        sum += total;
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            if (first + k < a.tiles) {
+                a.counts[first + k] = at;
+                at += c[k];
+            }
+    }
+    if (t == 0) {
+        a.sel->kstar = kstar;
+        a.sel->kept = sum;
+        host[0] = sum;
+        host[1] = 0ull;
+    }
+}
+
+// The kept items in order: put(item of the tile, its place, the number of them all).
+template <class ITEMS, class PUT>
+__global__ __launch_bounds__(kVolBlock) void k_select_emit(ITEMS items, SelArgs a, PUT put) {
+    __shared__ uint16_t s_item[kItemTile];
+    if (a.sel->overflow) return;
+    const int t = blockIdx.x;
+    const int64_t m = (int64_t)a.sel->kept, at = a.counts[t];
+    if (at == (t + 1 < a.tiles ? (int64_t)a.counts[t + 1] : m)) return;
+    const uint64_t kstar = a.sel->kstar;
+    const int64_t base = (int64_t)t * kItemTile, first = base + threadIdx.x * kItemLane;
+    uint32_t keep = 0u, total;
+    for_keys(items.mask8(first, a.n), first, a, [&](int k, uint64_t key) { keep |= key <= kstar ? 1u << k : 0u; });
+    uint32_t r = block_scan<kVolBlock>((uint32_t)__popc(keep), total) - __popc(keep);
+#pragma unroll
+    for (int k = 0; k < kItemLane; k++)
+        if (keep >> k & 1u) s_item[r++] = (uint16_t)(threadIdx.x * kItemLane + k);
+    __syncthreads();
+    const PUT put_t = put.at_tile(base);
+    for (uint32_t i = threadIdx.x; i < total; i += kVolBlock) put_t((int)s_item[i], at + i, m);
+}
+
+// A kept voxel's Gaussian, planar [14][m].
+struct PutVoxel {
+    const uint16_t *vol;
+    float *P;
     double inv_n2;          // 2 / n
     double thr, range;
     double lo[3], hi[3];
     double sh_dc;           // value of the constant SH basis function
-    float log_scale, logit_opacity;
-};
+    float log_scale, logit_opacity, inv_n;
+    int n;
+    int64_t base;           // the tile's first voxel, (x0, y0, z0)
+    int x0, y0, z0;
 
-// Writes the kept voxels of its block at offsets[block] + (rank in the block),
-// planar [14][m].
-__global__ __launch_bounds__(kVolBlock) void k_seed_emit(const uint16_t *__restrict__ vol, int64_t nvox,
-                                                         int n, float thr, uint64_t seed, int ibits,
-                                                         uint64_t kstar, const uint32_t *__restrict__ offsets,
-                                                         SeedConst sc, int64_t m, float *__restrict__ P) {
-    __shared__ uint32_t s_wave[kVolBlock / 64];
-    const int64_t base = (int64_t)blockIdx.x * kVolTile + (int64_t)threadIdx.x * kVolIpt;
-    bool keep[kVolIpt];
-    uint32_t c = 0;
-#pragma unroll
-    for (int k = 0; k < kVolIpt; k++) {
-        keep[k] = base + k < nvox && kept(vol, base + k, thr, seed, ibits, kstar);
-        c += keep[k] ? 1u : 0u;
+    __device__ __forceinline__ PutVoxel at_tile(int64_t first) const {
+        PutVoxel p = *this;
+        p.base = first;
+        const int64_t row = first / n;
+        p.z0 = (int)(first - row * n);
+        p.x0 = (int)(row / n);
+        p.y0 = (int)(row - (int64_t)p.x0 * n);
+        return p;
     }
-    // exclusive scan of c over the block (threads in raster order)
-    const int lane = __lane_id(), w = threadIdx.x >> 6;
-    uint32_t inc = c;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += y;
-    }
-    if (lane == 63) s_wave[w] = inc;
-    __syncthreads();
-    uint32_t pos = offsets[blockIdx.x] + inc - c;
-    for (int k = 0; k < w; k++) pos += s_wave[k];
-#pragma unroll
-    for (int k = 0; k < kVolIpt; k++) {
-        if (!keep[k]) continue;
-        const int64_t i = base + k;
-        const int64_t ix = i / ((int64_t)n * n), iy = (i / n) % n, iz = i % n;
-        const double t0 = ((double)vol[i] - sc.thr) / sc.range;
+    // j / n for 0 <= j < n + kItemTile: half a unit is far more than the rounding.
+    __device__ __forceinline__ int over_n(int j) const { return (int)(((float)j + 0.5f) * inv_n); }
+    __device__ __forceinline__ void operator()(int item, int64_t at, int64_t m) const {
+        const int row = over_n(z0 + item), iz = z0 + item - row * n;
+        const int plane = over_n(y0 + row), iy = y0 + row - plane * n, ix = x0 + plane;
+        const double t0 = ((double)vol[base + item] - thr) / range;
         const double t = t0 < 0.0 ? 0.0 : (t0 > 1.0 ? 1.0 : t0);
-        float *p = P + pos;
-        p[0 * m] = (float)(((double)ix + 0.5) * sc.inv_n2 - 1.0);
-        p[1 * m] = (float)(((double)iy + 0.5) * sc.inv_n2 - 1.0);
-        p[2 * m] = (float)(((double)iz + 0.5) * sc.inv_n2 - 1.0);
-        p[3 * m] = p[4 * m] = p[5 * m] = sc.log_scale;
+        float *p = P + at;
+        p[0 * m] = (float)(((double)ix + 0.5) * inv_n2 - 1.0);
+        p[1 * m] = (float)(((double)iy + 0.5) * inv_n2 - 1.0);
+        p[2 * m] = (float)(((double)iz + 0.5) * inv_n2 - 1.0);
+        p[3 * m] = p[4 * m] = p[5 * m] = log_scale;
         p[6 * m] = 1.f;
         p[7 * m] = p[8 * m] = p[9 * m] = 0.f;
-        p[10 * m] = sc.logit_opacity;
+        p[10 * m] = logit_opacity;
 #pragma unroll
         for (int ch = 0; ch < 3; ch++) {
-            const double col = sc.lo[ch] * (1.0 - t) + sc.hi[ch] * t;
-            p[(11 + ch) * m] = (float)((col - 0.5) / sc.sh_dc);
+            const double col = lo[ch] * (1.0 - t) + hi[ch] * t;
+            p[(11 + ch) * m] = (float)((col - 0.5) / sh_dc);
         }
-        pos++;
     }
-}
+};
+
+// A kept ray's Gaussian, planar [14][m], and its number (ray_ids nullable).
+struct PutHit {
+    const float4 *pos, *col;
+    float *P;
+    int32_t *ray_ids;
+    float log_scale, logit_opacity, inv_sh_dc;
+    int64_t base;
+
+    __device__ __forceinline__ PutHit at_tile(int64_t first) const {
+        PutHit p = *this;
+        p.base = first;
+        return p;
+    }
+    __device__ __forceinline__ void operator()(int item, int64_t at, int64_t m) const {
+        const int64_t i = base + item;
+        const float4 p4 = pos[i], c4 = col[i];
+        float *p = P + at;
+        p[0 * m] = p4.x;
+        p[1 * m] = p4.y;
+        p[2 * m] = p4.z;
+        p[3 * m] = p[4 * m] = p[5 * m] = log_scale;
+        p[6 * m] = 1.f;
+        p[7 * m] = p[8 * m] = p[9 * m] = 0.f;
+        p[10 * m] = logit_opacity;
+        p[11 * m] = (c4.x - 0.5f) * inv_sh_dc;
+        p[12 * m] = (c4.y - 0.5f) * inv_sh_dc;
+        p[13 * m] = (c4.z - 0.5f) * inv_sh_dc;
+        if (ray_ids) ray_ids[at] = (int32_t)i;
+    }
+};
 
 // ---- ray march ---------------------------------------------------------------------
 // Both marches sample the volume about twice a voxel along every pixel's ray.  Most
@@ -518,177 +843,77 @@ __global__ __launch_bounds__(kMarchBlock) void k_first_hit(const uint16_t *__res
     col[ray] = make_float4(C[0] * ia, C[1] * ia, C[2] * ia, 0.f);
 }
 
-// Digit histogram of the hit rays whose priority agrees with `prefix` above `shift`.
-__global__ __launch_bounds__(kVolBlock) void k_hit_hist(const uint8_t *__restrict__ hit, int64_t nrays,
-                                                        uint64_t seed, int ibits, uint64_t prefix,
-                                                        int shift, unsigned long long *__restrict__ hist) {
-    __shared__ unsigned long long h[256];
-    for (int d = threadIdx.x; d < 256; d += kVolBlock) h[d] = 0ull;
-    __syncthreads();
-    const uint64_t above = shift >= 56 ? 0ull : (~0ull << (shift + 8));
-    for (int64_t i = (int64_t)blockIdx.x * kVolBlock + threadIdx.x; i < nrays;
-         i += (int64_t)gridDim.x * kVolBlock) {
-        if (!hit[i]) continue;
-        const uint64_t key = priority(seed, (uint64_t)i, ibits);
-        if ((key & above) != (prefix & above)) continue;
-        atomicAdd(&h[(key >> shift) & 0xFFu], 1ull);
-    }
-    __syncthreads();
-    for (int d = threadIdx.x; d < 256; d += kVolBlock)
-        if (h[d]) atomicAdd(&hist[d], h[d]);
-}
-
-__device__ __forceinline__ bool hit_kept(const uint8_t *hit, int64_t i, uint64_t seed, int ibits,
-                                         uint64_t kstar) {
-    return hit[i] && priority(seed, (uint64_t)i, ibits) <= kstar;
-}
-
-// Kept rays per block of kVolTile rays.
-__global__ __launch_bounds__(kVolBlock) void k_hit_count(const uint8_t *__restrict__ hit, int64_t nrays,
-                                                         uint64_t seed, int ibits, uint64_t kstar,
-                                                         uint32_t *__restrict__ counts) {
-    __shared__ uint32_t s_c;
-    if (threadIdx.x == 0) s_c = 0u;
-    __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kVolTile + (int64_t)threadIdx.x * kVolIpt;
-    uint32_t c = 0;
-#pragma unroll
-    for (int k = 0; k < kVolIpt; k++) c += base + k < nrays && hit_kept(hit, base + k, seed, ibits, kstar) ? 1u : 0u;
-    if (c) atomicAdd(&s_c, c);
-    __syncthreads();
-    if (threadIdx.x == 0) counts[blockIdx.x] = s_c;
-}
-
-struct HitEmit {
-    float log_scale, logit_opacity, inv_sh_dc;
-};
-
-// Gaussians of the kept rays, in ray order, planar [14][m]; ray_ids nullable.
-__global__ __launch_bounds__(kVolBlock) void k_hit_emit(const uint8_t *__restrict__ hit, int64_t nrays,
-                                                        uint64_t seed, int ibits, uint64_t kstar,
-                                                        const uint32_t *__restrict__ offsets,
-                                                        const float4 *__restrict__ pos,
-                                                        const float4 *__restrict__ col, HitEmit he,
-                                                        int64_t m, float *__restrict__ P,
-                                                        int32_t *__restrict__ ray_ids) {
-    __shared__ uint32_t s_wave[kVolBlock / 64];
-    const int64_t base = (int64_t)blockIdx.x * kVolTile + (int64_t)threadIdx.x * kVolIpt;
-    bool keep[kVolIpt];
-    uint32_t c = 0;
-#pragma unroll
-    for (int k = 0; k < kVolIpt; k++) {
-        keep[k] = base + k < nrays && hit_kept(hit, base + k, seed, ibits, kstar);
-        c += keep[k] ? 1u : 0u;
-    }
-    const int lane = __lane_id(), w = threadIdx.x >> 6;
-    uint32_t inc = c;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += y;
-    }
-    if (lane == 63) s_wave[w] = inc;
-    __syncthreads();
-    uint32_t at = offsets[blockIdx.x] + inc - c;
-    for (int k = 0; k < w; k++) at += s_wave[k];
-#pragma unroll
-    for (int k = 0; k < kVolIpt; k++) {
-        if (!keep[k]) continue;
-        const int64_t i = base + k;
-        const float4 p4 = pos[i], c4 = col[i];
-        float *p = P + at;
-        p[0 * m] = p4.x;
-        p[1 * m] = p4.y;
-        p[2 * m] = p4.z;
-        p[3 * m] = p[4 * m] = p[5 * m] = he.log_scale;
-        p[6 * m] = 1.f;
-        p[7 * m] = p[8 * m] = p[9 * m] = 0.f;
-        p[10 * m] = he.logit_opacity;
-        p[11 * m] = (c4.x - 0.5f) * he.inv_sh_dc;
-        p[12 * m] = (c4.y - 0.5f) * he.inv_sh_dc;
-        p[13 * m] = (c4.z - 0.5f) * he.inv_sh_dc;
-        if (ray_ids) ray_ids[at] = (int32_t)i;
-        at++;
-    }
-}
-
 }  // namespace
 
-int seed_blocks(int64_t nvox) { return (int)((nvox + kVolTile - 1) / kVolTile); }
+namespace {
+size_t occupancy_bytes() { return (size_t)kOccSide * kOccSide * kOccSide / 8; }
 
-// Host side of the seeding (synchronises the stream several times).
-hipError_t run_seed(hipStream_t s, const uint16_t *vol, int n, double thr, double range,
-                    const double *lo, const double *hi, double opacity, int64_t cap, uint64_t seed,
-                    float *params, int64_t *count, void *scratch) {
-    const int64_t nvox = (int64_t)n * n * n;
-    int ibits = 0;
-    while ((int64_t(1) << ibits) < nvox) ibits++;
-    if (ibits < 1) ibits = 1;
-    unsigned long long *hist = (unsigned long long *)scratch;                 // 256
-    uint32_t *counts = (uint32_t *)((char *)scratch + 256 * sizeof(unsigned long long));
-    const int nb = seed_blocks(nvox);
-    std::vector<unsigned long long> h(256);
-    std::vector<uint32_t> cnt(nb);
-    int grid = nb < 1024 ? nb : 1024;
-    // MSB-first radix select of the cap-th smallest priority among the candidates
-    uint64_t prefix = 0;
-    int64_t rank = cap;          // 1-based rank still to find within the prefix
-    int64_t total = -1;
-    for (int shift = 56; shift >= 0; shift -= 8) {
-        hipError_t e = hipMemsetAsync(hist, 0, 256 * sizeof(unsigned long long), s);
+int item_tiles(int64_t n) { return (int)((n + kItemTile - 1) / kItemTile); }
+
+// The items of the cap smallest priorities, written by `put`; their number to *count.
+// counts: item_tiles(n); synchronises the stream.
+template <class ITEMS, class PUT>
+hipError_t run_select(hipStream_t s, const ITEMS &items, const PUT &put, int64_t n, int64_t cap, uint64_t seed,
+                      uint32_t *counts, const VolumeScratch &vs, int cus, int64_t *count) {
+    SelArgs a{};
+    a.n = n;
+    a.cap = cap;
+    a.seed = seed;
+    while ((int64_t(1) << a.ibits) < n) a.ibits++;
+    if (a.ibits < 1) a.ibits = 1;
+    a.tiles = item_tiles(n);
+    a.sel = (Selection *)((char *)vs.device + occupancy_bytes());
+    a.counts = counts;
+    const int grid = std::min((4 * a.tiles + kSelBlock / 64 - 1) / (kSelBlock / 64), 2 * cus);   // what the device holds
+    int levels = 1;
+    while (levels < kMaxLevels && (n >> (kDigitBits * levels)) > kUndecided) levels++;
+    for (;; levels++) {
+        k_select_clear<<<(std::max(levels * kDigits, a.tiles) + kVolBlock - 1) / kVolBlock, kVolBlock, 0, s>>>(a, levels);
+        for (int l = 0; l < levels; l++) k_select_hist<<<grid, kSelBlock, 0, s>>>(items, a, l);
+        k_select_collect<<<grid, kSelBlock, 0, s>>>(items, a, levels);
+        k_select_finish<<<1, 1024, 0, s>>>(a, levels, vs.host);
+        k_select_emit<<<a.tiles, kVolBlock, 0, s>>>(items, a, put);
+        hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        k_seed_hist<<<grid, kVolBlock, 0, s>>>(vol, nvox, (float)thr, seed, ibits, prefix, shift, hist);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = hipMemcpyAsync(h.data(), hist, 256 * sizeof(unsigned long long), hipMemcpyDeviceToHost, s)) != hipSuccess)
-            return e;
         if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-        if (total < 0) {
-            total = 0;
-            for (int d = 0; d < 256; d++) total += (int64_t)h[d];
-            if (total <= cap) {     // every candidate is kept
-                prefix = ~0ull;
-                rank = 0;
-                break;
-            }
-        }
-        int d = 0;
-        while (d < 255 && (int64_t)h[d] < rank) rank -= (int64_t)h[d++];
-        prefix |= (uint64_t)d << shift;
+        if (!vs.host[1] || levels == kMaxLevels) break;
     }
-    const uint64_t kstar = prefix;   // priorities are distinct: exactly min(total, cap) are <= kstar
-    k_seed_count<<<nb, kVolBlock, 0, s>>>(vol, nvox, (float)thr, seed, ibits, kstar, counts);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if ((e = hipMemcpyAsync(cnt.data(), counts, nb * sizeof(uint32_t), hipMemcpyDeviceToHost, s)) != hipSuccess)
-        return e;
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-    int64_t m = 0;
-    for (int b = 0; b < nb; b++) {
-        const uint32_t c = cnt[b];
-        cnt[b] = (uint32_t)m;
-        m += c;
-    }
-    if ((e = hipMemcpyAsync(counts, cnt.data(), nb * sizeof(uint32_t), hipMemcpyHostToDevice, s)) != hipSuccess)
-        return e;
-    SeedConst sc;
-    sc.inv_n2 = 2.0 / n;
-    sc.thr = thr;
-    sc.range = range;
-    for (int c = 0; c < 3; c++) {
-        sc.lo[c] = lo[c];
-        sc.hi[c] = hi[c];
-    }
-    sc.sh_dc = 0.5 / std::sqrt(std::acos(-1.0));
-    sc.log_scale = (float)std::log(2.0 / n);
-    sc.logit_opacity = (float)std::log(opacity / (1.0 - opacity));
-    k_seed_emit<<<nb, kVolBlock, 0, s>>>(vol, nvox, n, (float)thr, seed, ibits, kstar, counts, sc, m, params);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-    *count = m;
+    *count = (int64_t)vs.host[0];
     return hipSuccess;
 }
+}  // namespace
 
-size_t seed_scratch_bytes(int64_t nvox) { return 256 * sizeof(unsigned long long) + (size_t)seed_blocks(nvox) * 4; }
+// Host side of the seeding (synchronises the stream).
+hipError_t run_seed(hipStream_t s, const uint16_t *vol, int n, double thr, double range,
+                    const double *lo, const double *hi, double opacity, int64_t cap, uint64_t seed,
+                    float *params, int64_t *count, void *scratch, const VolumeScratch &vs, int cus) {
+    if (!vs.device) return hipErrorStreamCaptureUnsupported;   // the call synchronises
+    const int64_t nvox = (int64_t)n * n * n;
+    VoxelItems items{};
+    items.vol = vol;
+    const float thr_f = (float)thr;   // value > thr_f, for whole values
+    items.least = thr_f < 0.f ? 0u : (thr_f < 65535.f ? (uint32_t)thr_f + 1u : 65536u);   // NaN: none
+    items.wide = ((uintptr_t)vol & 15u) == 0;
+    PutVoxel put{};
+    put.vol = vol;
+    put.P = params;
+    put.n = n;
+    put.inv_n = 1.f / (float)n;
+    put.inv_n2 = 2.0 / n;
+    put.thr = thr;
+    put.range = range;
+    for (int c = 0; c < 3; c++) {
+        put.lo[c] = lo[c];
+        put.hi[c] = hi[c];
+    }
+    put.sh_dc = 0.5 / std::sqrt(std::acos(-1.0));
+    put.log_scale = (float)std::log(2.0 / n);
+    put.logit_opacity = (float)std::log(opacity / (1.0 - opacity));
+    uint32_t *counts = (uint32_t *)((char *)scratch + 256 * sizeof(unsigned long long));
+    return run_select(s, items, put, nvox, cap, seed, counts, vs, cus, count);
+}
+
+size_t seed_scratch_bytes(int64_t nvox) { return 256 * sizeof(unsigned long long) + (size_t)item_tiles(nvox) * 4; }
 
 namespace {
 size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
@@ -725,11 +950,11 @@ OccGrid build_occupancy(hipStream_t s, const uint16_t *vol, int n, float thr, fl
 }
 }  // namespace
 
-size_t occupancy_bytes() { return (size_t)kOccSide * kOccSide * kOccSide / 8; }
+size_t volume_scratch_bytes() { return occupancy_bytes() + sizeof(Selection); }
 
 size_t first_hit_scratch_bytes(int64_t nrays) {
     return round256((size_t)nrays) + 2 * round256((size_t)nrays * 16) +
-           256 * sizeof(unsigned long long) + (size_t)seed_blocks(nrays) * 4;
+           256 * sizeof(unsigned long long) + (size_t)item_tiles(nrays) * 4;
 }
 
 hipError_t run_first_hits(hipStream_t s, const uint16_t *vol, int n, const gsf_camera *cams,
@@ -737,7 +962,8 @@ hipError_t run_first_hits(hipStream_t s, const uint16_t *vol, int n, const gsf_c
                           float extinction, float thr, float range, const float *lo, const float *hi,
                           float hit_alpha, int color_steps, double opacity, int64_t cap,
                           uint64_t seed, float *params, int64_t *count, int32_t *ray_ids,
-                          void *scratch, void *occ) {
+                          void *scratch, const VolumeScratch &vs, int cus) {
+    if (!vs.device) return hipErrorStreamCaptureUnsupported;   // the call synchronises
     const RayViews rv = ray_views(nviews, widths, heights);
     const int64_t nrays = rv.off[nviews];
     char *sp = (char *)scratch;
@@ -747,7 +973,6 @@ hipError_t run_first_hits(hipStream_t s, const uint16_t *vol, int n, const gsf_c
     sp += round256((size_t)nrays * 16);
     float4 *col = (float4 *)sp;
     sp += round256((size_t)nrays * 16);
-    unsigned long long *hist = (unsigned long long *)sp;
     uint32_t *counts = (uint32_t *)(sp + 256 * sizeof(unsigned long long));
     MarchConst mc{};
     mc.n = n;
@@ -761,70 +986,23 @@ hipError_t run_first_hits(hipStream_t s, const uint16_t *vol, int n, const gsf_c
         mc.lo[c] = lo[c];
         mc.hi[c] = hi[c];
     }
-    const OccGrid og = build_occupancy(s, vol, n, thr, extinction, occ);
+    const OccGrid og = build_occupancy(s, vol, n, thr, extinction, vs.device);
     k_first_hit<<<rv.block[nviews], kMarchBlock, 0, s>>>(vol, cams, rv, mc, og, hit, pos, col);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    int ibits = 0;
-    while ((int64_t(1) << ibits) < nrays) ibits++;
-    if (ibits < 1) ibits = 1;
-    const int nb = seed_blocks(nrays);
-    std::vector<unsigned long long> h(256);
-    std::vector<uint32_t> cnt(nb);
-    const int grid = nb < 1024 ? nb : 1024;
-    // MSB-first radix select of the cap-th smallest priority among the hit rays
-    uint64_t prefix = 0;
-    int64_t rank = cap;
-    int64_t total = -1;
-    for (int shift = 56; shift >= 0; shift -= 8) {
-        if ((e = hipMemsetAsync(hist, 0, 256 * sizeof(unsigned long long), s)) != hipSuccess) return e;
-        k_hit_hist<<<grid, kVolBlock, 0, s>>>(hit, nrays, seed, ibits, prefix, shift, hist);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = hipMemcpyAsync(h.data(), hist, 256 * sizeof(unsigned long long), hipMemcpyDeviceToHost, s)) != hipSuccess)
-            return e;
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-        if (total < 0) {
-            total = 0;
-            for (int d = 0; d < 256; d++) total += (int64_t)h[d];
-            if (total <= cap) {     // every hit is kept
-                prefix = ~0ull;
-                break;
-            }
-        }
-        int d = 0;
-        while (d < 255 && (int64_t)h[d] < rank) rank -= (int64_t)h[d++];
-        prefix |= (uint64_t)d << shift;
-    }
-    const uint64_t kstar = prefix;   // priorities are distinct: min(total, cap) are <= kstar
-    k_hit_count<<<nb, kVolBlock, 0, s>>>(hit, nrays, seed, ibits, kstar, counts);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = hipMemcpyAsync(cnt.data(), counts, nb * sizeof(uint32_t), hipMemcpyDeviceToHost, s)) != hipSuccess)
-        return e;
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-    int64_t m = 0;
-    for (int b = 0; b < nb; b++) {
-        const uint32_t c = cnt[b];
-        cnt[b] = (uint32_t)m;
-        m += c;
-    }
-    if ((e = hipMemcpyAsync(counts, cnt.data(), nb * sizeof(uint32_t), hipMemcpyHostToDevice, s)) != hipSuccess)
-        return e;
-    HitEmit he;
-    he.log_scale = (float)std::log(2.0 / n);
-    he.logit_opacity = (float)std::log(opacity / (1.0 - opacity));
-    he.inv_sh_dc = (float)(1.0 / (0.5 / std::sqrt(std::acos(-1.0))));
-    k_hit_emit<<<nb, kVolBlock, 0, s>>>(hit, nrays, seed, ibits, kstar, counts, pos, col, he, m,
-                                       params, ray_ids);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-    *count = m;
-    return hipSuccess;
+    PutHit put{};
+    put.pos = pos;
+    put.col = col;
+    put.P = params;
+    put.ray_ids = ray_ids;
+    put.log_scale = (float)std::log(2.0 / n);
+    put.logit_opacity = (float)std::log(opacity / (1.0 - opacity));
+    put.inv_sh_dc = (float)(1.0 / (0.5 / std::sqrt(std::acos(-1.0))));
+    return run_select(s, RayItems{hit}, put, nrays, cap, seed, counts, vs, cus, count);
 }
 
 hipError_t run_raymarch(hipStream_t s, const uint16_t *vol, int n, const gsf_camera *cams, int nviews,
                         const int32_t *widths, const int32_t *heights, float step, float extinction,
                         float t_stop, float thr, float range, const float *lo, const float *hi,
-                        float *out, void *occ) {
+                        float *out, const VolumeScratch &vs) {
     MarchConst mc{};
     mc.n = n;
     mc.step = step;
@@ -837,7 +1015,7 @@ hipError_t run_raymarch(hipStream_t s, const uint16_t *vol, int n, const gsf_cam
         mc.hi[c] = hi[c];
     }
     const RayViews rv = ray_views(nviews, widths, heights);
-    const OccGrid og = build_occupancy(s, vol, n, thr, extinction, occ);
+    const OccGrid og = build_occupancy(s, vol, n, thr, extinction, vs.device);
     k_raymarch<<<rv.block[nviews], kMarchBlock, 0, s>>>(vol, cams, rv, mc, og, out);
     return hipGetLastError();
 }
