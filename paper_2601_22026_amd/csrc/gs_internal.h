@@ -424,12 +424,12 @@ struct TileMap {
 // written for the same gaze and radius).  block_sums[b] / block_act[b]
 // receive the total count / the number of records with a nonzero count among
 // records 256 b .. 256 b + 255 (scan_blocks(nrec) words each), the input of
-// launch_scan_records.
+// launch_scan_records and launch_scan_bin.  clear[nclear] (nullable) is zeroed.
 void launch_project_fwd(hipStream_t s, const float *P, int n, int nviews, int deg,
                         const gsf_camera *cams, const ViewDesc *views, int tile, SplatPtrs sp,
                         uint32_t *depth_key, uint2 *rect, uint32_t *count, uint2 *rspan,
                         const float *cull_gaze, float cull_radius, const FoveaRows &fr,
-                        uint32_t *block_sums, uint32_t *block_act);
+                        uint32_t *block_sums, uint32_t *block_act, uint32_t *clear, int nclear);
 // The row table of fovea culling: fr.rows[v * fr.per_view + ty] for every view
 // and tile row up to fr.per_view (rows past a view's last: none).
 void launch_fovea_rows(hipStream_t s, const float *gaze, float radius_frac, const ViewDesc *views,
@@ -475,6 +475,26 @@ void launch_emit(hipStream_t s, const uint32_t *dval, const uint32_t *a_dev, con
                  int64_t capacity, const TileMap &tm, uint32_t *keys, uint32_t *vals);
 int seg_count(int64_t nrec);
 int scan_blocks(int64_t nrec);
+
+// Small plans: the same lists (and ranges, order, koff, row tables) in three launches
+// in place of launch_scan_records, launch_depth_sort, launch_emit,
+// launch_radix_sort, launch_tile_bounds and launch_tile_order.  binned_lists: whether
+// the plan's sizes allow it (nrec records; arec_bytes: room for `totals`).
+//   launch_scan_bin: totals[total_tiles] are clear; keys to (bkey, brec) in record order;
+//   launch_bin_place: ranges, order, and each key's (depth bits, record) in its tile's
+//   range of (pdepth, prec);
+//   launch_bin_sort: prec sorted per tile (qdepth, qrec: scratch).
+bool binned_lists(int64_t nrec, int64_t total_tiles, int64_t arec_bytes);
+void launch_scan_bin(hipStream_t s, const uint32_t *count, const uint2 *rect, const uint2 *rspan, SplatPtrs sp,
+                     uint32_t *koff, uint2 *rowtab, int nrec, int n, int tile, const ViewDesc *views, int nviews,
+                     const FoveaRows &fr, const uint32_t *block_sums, const uint32_t *block_act, uint32_t *m_dev,
+                     unsigned long long *m_total, uint32_t *a_dev, uint32_t *flags, int64_t capacity,
+                     int total_tiles, uint32_t *totals, uint32_t *bkey, uint32_t *brec);
+void launch_bin_place(hipStream_t s, const uint32_t *totals, int total_tiles, int64_t capacity, const uint32_t *bkey,
+                      const uint32_t *brec, const uint32_t *depth_key, uint32_t *pdepth, uint32_t *prec,
+                      uint2 *ranges, uint32_t *order);
+void launch_bin_sort(hipStream_t s, const uint2 *ranges, const uint32_t *order, int total_tiles,
+                     uint32_t *pdepth, uint32_t *prec, uint32_t *qdepth, uint32_t *qrec);
 
 // Stable LSD radix sort of (key, value) pairs by the low `bits` key bits in
 // radix_passes(bits) passes of at most 8-bit digits; the count is read from

@@ -400,19 +400,29 @@ gsf_status enqueue_forward(gsf_plan *p, const float *params, int64_t n, const gs
         gsf_status fs = flush_timing(p);
         if (fs != GSF_OK) return fs;
     }
+    // small plans: the keys binned by tile, each list sorted by itself
+    const bool binned = !cull_gaze && binned_lists(nrec, p->total_tiles,
+                                                   std::min<int64_t>(p->nrec_max, p->cap) * 32);
+    uint32_t *totals = (uint32_t *)b.arec;
     {   // splats, support boxes and their tile counts, depth keys
         StageTimer t(p, GSF_STAGE_PROJECT);
         const FoveaRows fr{cull_gaze ? b.fovea_rows : nullptr, fovea_rows_per_view(p)};
         if (cull_gaze) launch_fovea_rows(s, cull_gaze, cull_radius, b.views, p->V, p->tile, fr);
         launch_project_fwd(s, params, (int)n, p->V, p->deg, cams, b.views, p->tile, splats(p),
                            b.depth_key, b.rect, b.count, b.rspan, cull_gaze, cull_radius, fr,
-                           b.block_sums, b.block_act);
+                           b.block_sums, b.block_act, binned ? totals : nullptr,
+                           binned ? (int)p->total_tiles : 0);
     }
     GSF_LAUNCHED(ctx);
     {   // record-order scan: gradient slots, row tables, key total + capacity check on
         // the device; the records with keys compacted with their depths
         StageTimer t(p, GSF_STAGE_DUPLICATE);
-        launch_scan_records(s, b.count, b.rect, b.rspan, splats(p), b.depth_key, b.koff,
+        if (binned)
+            launch_scan_bin(s, b.count, b.rect, b.rspan, splats(p), b.koff, b.rowtab, nrec, (int)n, p->tile,
+                            b.views, p->V, FoveaRows{}, b.block_sums, b.block_act, b.m_dev, b.m_total, b.a_dev,
+                            b.flags, p->cap, (int)p->total_tiles, totals, b.k1, b.v1);
+        else
+            launch_scan_records(s, b.count, b.rect, b.rspan, splats(p), b.depth_key, b.koff,
                             b.rowtab, nrec, (int)n, p->tile, b.views,
                             FoveaRows{cull_gaze ? b.fovea_rows : nullptr, fovea_rows_per_view(p)},
                             b.block_sums, b.block_act,
@@ -446,31 +456,47 @@ gsf_status enqueue_forward(gsf_plan *p, const float *params, int64_t n, const gs
     const int64_t ltiles = tm.gaze ? (int64_t)p->V * tm.box * tm.box : p->total_tiles;
     p->fwd_tm = tm;
     p->fwd_tiles = ltiles;
-    {   // depth order of the records with keys (stable: equal depths keep the
-        // record order), then their keys emitted in that order
-        StageTimer t(p, GSF_STAGE_DEPTH_SORT);
-        launch_depth_sort(s, b.k0, b.v0, b.k1, b.v1, b.a_dev, p->radix_grid, b.hist, b.digit_tot,
-                          b.depth_mm, b.depth_ctl, b.dsorted);
-        launch_emit(s, b.dsorted, b.a_dev, b.arec, b.rowtab, nrec, (int)n, b.views, p->V,
-                    b.emit_sums, b.seg_tot, b.m_total, p->cap, tm, b.ek, b.ev);
+    if (binned) {
+        {   // the tiles' ranges and order, the keys into their tiles
+            StageTimer t(p, GSF_STAGE_TILE_SORT);
+            launch_bin_place(s, totals, (int)p->total_tiles, p->cap, b.k1, b.v1, b.depth_key, b.k0, b.v0,
+                             b.ranges, b.order);
+        }
+        GSF_LAUNCHED(ctx);
+        {   // each tile's keys by (depth, record)
+            StageTimer t(p, GSF_STAGE_DEPTH_SORT);
+            launch_bin_sort(s, b.ranges, b.order, (int)p->total_tiles, b.k0, b.v0, b.k1, b.v1);
+        }
+        { StageTimer t(p, GSF_STAGE_RANGES); }   // done by launch_bin_place
+        p->b.vals = b.v0;
+        GSF_LAUNCHED(ctx);
+    } else {
+        {   // depth order of the records with keys (stable: equal depths keep the
+            // record order), then their keys emitted in that order
+            StageTimer t(p, GSF_STAGE_DEPTH_SORT);
+            launch_depth_sort(s, b.k0, b.v0, b.k1, b.v1, b.a_dev, p->radix_grid, b.hist, b.digit_tot,
+                              b.depth_mm, b.depth_ctl, b.dsorted);
+            launch_emit(s, b.dsorted, b.a_dev, b.arec, b.rowtab, nrec, (int)n, b.views, p->V,
+                        b.emit_sums, b.seg_tot, b.m_total, p->cap, tm, b.ek, b.ev);
+        }
+        GSF_LAUNCHED(ctx);
+        {   // stable by tile: each tile's keys stay in (depth, record) order
+            StageTimer t(p, GSF_STAGE_TILE_SORT);
+            const int grid = p->host_sized ? radix_grid_for(p->m_host) : p->radix_grid;
+            const int where = launch_radix_sort(s, b.ek, b.ev, b.tk, b.tv, b.ek, b.ev, m_dev, p->m_host,
+                                                sort_bits, grid, b.hist, b.digit_tot);
+            p->b.keys = where == 1 ? b.tk : b.ek;   // the sorted pair (passes depend on the key space)
+            p->b.vals = where == 1 ? b.tv : b.ev;
+        }
+        GSF_LAUNCHED(ctx);
+        {
+            StageTimer t(p, GSF_STAGE_RANGES);
+            launch_tile_bounds(s, b.keys, m_dev, p->m_host, p->cap, (int)ltiles, b.views, p->V,
+                               TileMap{}, b.ranges);
+            launch_tile_order(s, b.ranges, (int)ltiles, b.order, b.order_counts);
+        }
+        GSF_LAUNCHED(ctx);
     }
-    GSF_LAUNCHED(ctx);
-    {   // stable by tile: each tile's keys stay in (depth, record) order
-        StageTimer t(p, GSF_STAGE_TILE_SORT);
-        const int grid = p->host_sized ? radix_grid_for(p->m_host) : p->radix_grid;
-        const int where = launch_radix_sort(s, b.ek, b.ev, b.tk, b.tv, b.ek, b.ev, m_dev, p->m_host,
-                                            sort_bits, grid, b.hist, b.digit_tot);
-        p->b.keys = where == 1 ? b.tk : b.ek;   // the sorted pair (passes depend on the key space)
-        p->b.vals = where == 1 ? b.tv : b.ev;
-    }
-    GSF_LAUNCHED(ctx);
-    {
-        StageTimer t(p, GSF_STAGE_RANGES);
-        launch_tile_bounds(s, b.keys, m_dev, p->m_host, p->cap, (int)ltiles, b.views, p->V,
-                           TileMap{}, b.ranges);
-        launch_tile_order(s, b.ranges, (int)ltiles, b.order, b.order_counts);
-    }
-    GSF_LAUNCHED(ctx);
     {
         StageTimer t(p, GSF_STAGE_RENDER);
         RenderArgs ra = render_args(p, cams, n);

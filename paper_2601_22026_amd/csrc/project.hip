@@ -408,7 +408,9 @@ __global__ __launch_bounds__(256) void k_project_fwd_views(const float *__restri
 // per lane in one 16-byte load (the count array is 256-byte aligned).
 __global__ __launch_bounds__(256) void k_block_totals(const uint32_t *__restrict__ count, int nrec,
                                                       uint32_t *__restrict__ block_sums,
-                                                      uint32_t *__restrict__ block_act) {
+                                                      uint32_t *__restrict__ block_act,
+                                                      uint32_t *__restrict__ clear, int nclear) {
+    for (int i = blockIdx.x * 256 + (int)threadIdx.x; i < nclear; i += (int)gridDim.x * 256) clear[i] = 0u;
     const int bb = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
     if (bb * 256 >= nrec) return;
     const int lane = (int)(threadIdx.x & 63), r0 = bb * 256 + lane * 4;
@@ -447,9 +449,11 @@ __global__ __launch_bounds__(256) void k_project_fwd(const float *__restrict__ P
                                                      const float *__restrict__ cull_gaze,
                                                      float cull_radius, FoveaRows fr,
                                                      uint32_t *__restrict__ block_sums,
-                                                     uint32_t *__restrict__ block_act) {
+                                                     uint32_t *__restrict__ block_act,
+                                                     uint32_t *__restrict__ clear, int nclear) {
     __shared__ uint32_t s_w[4], s_a[4];
     const int r = blockIdx.x * 256 + (int)threadIdx.x;
+    for (int i = r; i < nclear; i += (int)gridDim.x * 256) clear[i] = 0u;
     uint32_t c = r < nrec ? project_record<DEG>(P, n, r, cams, views, tile, sp, depth_key, rect, count,
                                                 rspan, cull_gaze, cull_radius, fr)
                           : 0u;
@@ -678,7 +682,7 @@ void launch_project_fwd(hipStream_t s, const float *P, int n, int nviews, int de
                         uint32_t *depth_key, uint2 *rect, uint32_t *count, uint2 *rspan,
                         const float *cull_gaze, float cull_radius, const FoveaRows &fr,
                         uint32_t *block_sums,
-                        uint32_t *block_act) {
+                        uint32_t *block_act, uint32_t *clear, int nclear) {
     const int nrec = n * nviews;
     const dim3 grid((nrec + 255) / 256), block(256);
     if (deg <= 1 && nviews > 1) {   // one thread per Gaussian for all views, then the block totals
@@ -689,14 +693,14 @@ void launch_project_fwd(hipStream_t s, const float *P, int n, int nviews, int de
         else
             k_project_fwd_views<1><<<ggrid, block, 0, s>>>(P, n, nviews, cams, views, tile, sp, depth_key,
                                                             rect, count, rspan, cull_gaze, cull_radius, fr);
-        k_block_totals<<<(nrec + 1023) / 1024, block, 0, s>>>(count, nrec, block_sums, block_act);
+        k_block_totals<<<(nrec + 1023) / 1024, block, 0, s>>>(count, nrec, block_sums, block_act, clear, nclear);
         return;
     }
     switch (deg) {
-    case 0: k_project_fwd<0><<<grid, block, 0, s>>>(P, n, nrec, cams, views, tile, sp, depth_key, rect, count, rspan, cull_gaze, cull_radius, fr, block_sums, block_act); break;
-    case 1: k_project_fwd<1><<<grid, block, 0, s>>>(P, n, nrec, cams, views, tile, sp, depth_key, rect, count, rspan, cull_gaze, cull_radius, fr, block_sums, block_act); break;
-    case 2: k_project_fwd<2><<<grid, block, 0, s>>>(P, n, nrec, cams, views, tile, sp, depth_key, rect, count, rspan, cull_gaze, cull_radius, fr, block_sums, block_act); break;
-    default: k_project_fwd<3><<<grid, block, 0, s>>>(P, n, nrec, cams, views, tile, sp, depth_key, rect, count, rspan, cull_gaze, cull_radius, fr, block_sums, block_act); break;
+    case 0: k_project_fwd<0><<<grid, block, 0, s>>>(P, n, nrec, cams, views, tile, sp, depth_key, rect, count, rspan, cull_gaze, cull_radius, fr, block_sums, block_act, clear, nclear); break;
+    case 1: k_project_fwd<1><<<grid, block, 0, s>>>(P, n, nrec, cams, views, tile, sp, depth_key, rect, count, rspan, cull_gaze, cull_radius, fr, block_sums, block_act, clear, nclear); break;
+    case 2: k_project_fwd<2><<<grid, block, 0, s>>>(P, n, nrec, cams, views, tile, sp, depth_key, rect, count, rspan, cull_gaze, cull_radius, fr, block_sums, block_act, clear, nclear); break;
+    default: k_project_fwd<3><<<grid, block, 0, s>>>(P, n, nrec, cams, views, tile, sp, depth_key, rect, count, rspan, cull_gaze, cull_radius, fr, block_sums, block_act, clear, nclear); break;
     }
 }
 

@@ -24,7 +24,10 @@
 //      (peer masks) and combines the waves in order (stable);
 //   5. tile ranges from the boundaries of the sorted keys, and the compositing
 //      order (tiles with more keys first).
-// Depth bits of positive floats order like the floats.
+// Depth bits of positive floats order like the floats.  Plans of few records and tiles
+// (binned_lists) come to the same lists in three launches, without steps 2 to 4.
+#include <algorithm>
+
 #include "gs_internal.h"
 
 namespace gsf {
@@ -485,18 +488,10 @@ __device__ __forceinline__ bool block_prefix(const uint32_t *__restrict__ sums,
     return total_keys <= (unsigned long long)capacity;
 }
 
-// One record with keys: its compacted entry e (depth key, value, arec) and,
-// for a box not packed, its row table at its first gradient slot.
-__device__ __forceinline__ void scan_rec_place(uint32_t r, uint32_t c, uint32_t first, uint32_t e,
-                                               uint2 rc, uint2 pk, uint32_t dk, const SplatPtrs &sp,
-                                               uint2 *__restrict__ rowtab, int n, int tile,
-                                               const ViewDesc *__restrict__ views, const FoveaRows &fr,
-                                               uint32_t *__restrict__ dkey, uint32_t *__restrict__ dval,
-                                               uint4 *__restrict__ arec, const ValPack &vp) {
-    dkey[e] = dk;
-    dval[e] = vp.pack(e, c);
-    arec[2 * e] = make_uint4(r, first, c, pk.x);
-    arec[2 * e + 1] = make_uint4(rc.x, rc.y, pk.y, 0u);
+// The row table of a record whose box is not packed, at its first gradient slot.
+__device__ __forceinline__ void write_row_table(uint32_t r, uint32_t first, uint2 rc, uint2 pk,
+                                                const SplatPtrs &sp, uint2 *rowtab, int n, int tile,
+                                                const ViewDesc *__restrict__ views, const FoveaRows &fr) {
     const int x0 = (int)(rc.x & 0xFFFFu), y0 = (int)(rc.x >> 16);
     const int x1 = (int)(rc.y & 0xFFFFu), y1 = (int)(rc.y >> 16);
     if (y1 - y0 + 1 > kPackRows || x1 - x0 + 1 > kPackCols) {   // the row table
@@ -517,6 +512,21 @@ __device__ __forceinline__ void scan_rec_place(uint32_t r, uint32_t c, uint32_t 
             j++;
         }
     }
+}
+
+// One record with keys: its compacted entry e (depth key, value, arec) and,
+// for a box not packed, its row table at its first gradient slot.
+__device__ __forceinline__ void scan_rec_place(uint32_t r, uint32_t c, uint32_t first, uint32_t e,
+                                               uint2 rc, uint2 pk, uint32_t dk, const SplatPtrs &sp,
+                                               uint2 *__restrict__ rowtab, int n, int tile,
+                                               const ViewDesc *__restrict__ views, const FoveaRows &fr,
+                                               uint32_t *__restrict__ dkey, uint32_t *__restrict__ dval,
+                                               uint4 *__restrict__ arec, const ValPack &vp) {
+    dkey[e] = dk;
+    dval[e] = vp.pack(e, c);
+    arec[2 * e] = make_uint4(r, first, c, pk.x);
+    arec[2 * e + 1] = make_uint4(rc.x, rc.y, pk.y, 0u);
+    write_row_table(r, first, rc, pk, sp, rowtab, n, tile, views, fr);
 }
 
 // Record-order scan of the listed-tile counts: koff[r], the position of record
@@ -624,6 +634,47 @@ __global__ __launch_bounds__(kScanBlock) void k_emit_totals(const uint32_t *__re
     if (threadIdx.x == 0) sums[blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
 }
 
+// The tile (row ty, column tx) of key li of a record: a = (record, first slot, count,
+// spans.x or row-table size), b = (box, box, spans.y, -).
+__device__ __forceinline__ void key_tile(const uint4 &a, const uint4 &b, uint32_t li, const uint2 *rowtab,
+                                         uint32_t &ty, uint32_t &tx) {
+    const int x0 = (int)(b.x & 0xFFFFu), y0 = (int)(b.x >> 16);
+    const int x1 = (int)(b.y & 0xFFFFu), y1 = (int)(b.y >> 16);
+    ty = 0u;
+    tx = 0u;
+    if (y1 - y0 + 1 <= kPackRows && x1 - x0 + 1 <= kPackCols) {   // packed spans
+        for (int k = 0; k < kPackRows; k++) {
+            const uint32_t f = ((k < 2 ? a.w : b.z) >> (16 * (k & 1))) & 0xFFFFu;
+            const uint32_t w = f >> 8;
+            if (li < w) {
+                ty = (uint32_t)(y0 + k);
+                tx = (uint32_t)x0 + (f & 0xFFu) + li;
+                break;
+            }
+            li -= w;
+        }
+    } else {   // the last row-table entry whose key prefix is <= li holds key li
+        const uint32_t tb = a.y;
+        int ta = 0, tz = (int)a.w - 1;
+        while (ta < tz) {
+            const int mid = (ta + tz + 1) >> 1;
+            if (rowtab[tb + (uint32_t)mid].y <= li) ta = mid; else tz = mid - 1;
+        }
+        const uint2 te = rowtab[tb + (uint32_t)ta];
+        ty = (uint32_t)y0 + (te.x & 0xFFFFu);
+        tx = (te.x >> 16) + (li - te.y);
+    }
+}
+
+// The last of the block's records whose offset is <= q (slots past the records hold
+// the total; a record without keys is never the last): a fixed 8-step search.
+__device__ __forceinline__ int find_record(const uint32_t *s_off, uint32_t q) {
+    int lo = 0;
+#pragma unroll
+    for (int step = kScanTile / 2; step > 0; step >>= 1) lo = s_off[lo + step] <= q ? lo + step : lo;
+    return lo;
+}
+
 // Keys of the active records in depth order (key = global tile id, value =
 // record id): block b emits the keys of depth positions 256 b .. 256 b + 255,
 // all its threads together, key q of the block by thread q mod 256, the record
@@ -674,41 +725,11 @@ __global__ __launch_bounds__(kScanBlock) void k_emit(
     s_r1[threadIdx.x] = r1;
     __syncthreads();
     for (uint32_t q = threadIdx.x; q < total; q += kScanBlock) {
-        // the last record whose offset is <= q (every active record has keys;
-        // slots past the active records hold the total): a fixed 8-step search
-        int lo = 0;
-#pragma unroll
-        for (int step = kScanTile / 2; step > 0; step >>= 1)
-            lo = s_off[lo + step] <= q ? lo + step : lo;
-        uint32_t li = q - s_off[lo];              // index of the key within its record
+        const int lo = find_record(s_off, q);
         const uint4 a = s_r0[lo], b = s_r1[lo];
-        const uint32_t rr = a.x;
-        const int x0 = (int)(b.x & 0xFFFFu), y0 = (int)(b.x >> 16);
-        const int x1 = (int)(b.y & 0xFFFFu), y1 = (int)(b.y >> 16);
-        const uint32_t v = b.w;
-        uint32_t ty = 0u, tx = 0u;   // the key's tile
-        if (y1 - y0 + 1 <= kPackRows && x1 - x0 + 1 <= kPackCols) {   // packed spans
-            for (int k = 0; k < kPackRows; k++) {
-                const uint32_t f = ((k < 2 ? a.w : b.z) >> (16 * (k & 1))) & 0xFFFFu;
-                const uint32_t w = f >> 8;
-                if (li < w) {
-                    ty = (uint32_t)(y0 + k);
-                    tx = (uint32_t)x0 + (f & 0xFFu) + li;
-                    break;
-                }
-                li -= w;
-            }
-        } else {   // the last row-table entry whose key prefix is <= li holds key li
-            const uint32_t tb = a.y;
-            int ta = 0, tz = (int)a.w - 1;
-            while (ta < tz) {
-                const int mid = (ta + tz + 1) >> 1;
-                if (rowtab[tb + (uint32_t)mid].y <= li) ta = mid; else tz = mid - 1;
-            }
-            const uint2 te = rowtab[tb + (uint32_t)ta];
-            ty = (uint32_t)y0 + (te.x & 0xFFFFu);
-            tx = (te.x >> 16) + (li - te.y);
-        }
+        const uint32_t rr = a.x, v = b.w;
+        uint32_t ty, tx;   // the key's tile
+        key_tile(a, b, q - s_off[lo], rowtab, ty, tx);
         const ViewDesc vd = s_views[v];
         keys[gbase + q] = tm.gaze ? v * (uint32_t)(tm.box * tm.box) +
                                         (ty - (uint32_t)s_f0[v].y) * (uint32_t)tm.box +
@@ -957,6 +978,386 @@ __global__ __launch_bounds__(256) void k_order_place(const uint2 *__restrict__ r
     order_walk(ranges, total_tiles, s_cnt, order);
 }
 
+// ---- small plans: keys binned by tile, each tile's list sorted in LDS ----------------
+// The general path's two radix sorts take up to 24 launches, and at about 4.7 us each they
+// are most of the time that a plan of few records spends before compositing.  Where
+// the tiles' counters fit into LDS three launches do the same:
+// (k_scan_bin 8 to 20 us, k_bin_place 6 to 10, k_bin_sort 5 to 56 at the sizes below; what
+// bounds them is latency, and the longest list.)
+//   k_scan_bin   the record scan, and every record's keys in record order, each with
+//                its tile and its place within the tile's list: one workgroup counts in
+//                LDS, and one atomic add per (workgroup, tile) finds where its run starts
+//                (in any order);
+//   k_bin_place  the tiles' offsets, their ranges and the compositing order, and every
+//                key moved to its place;
+//   k_bin_sort   each tile's list sorted by (depth, record), which no two of its keys
+//                share: the lists are the general path's, whatever order the bins had.
+
+constexpr int kBinTiles = 8192;       // tiles whose counters fit into LDS
+constexpr int64_t kBinCrowd = 128;    // records a tile at most, on average
+constexpr int kBinSort = 4096;        // keys of a tile that are sorted in LDS
+
+// Key of the binned lists: its tile in the low `tbits` bits, its place in the tile above.
+__global__ __launch_bounds__(kScanBlock) void k_scan_bin(
+    const uint32_t *__restrict__ count, const uint2 *__restrict__ rect, const uint2 *__restrict__ rspan,
+    SplatPtrs sp, uint32_t *__restrict__ koff, uint2 *rowtab, int nrec, int n, int tile,
+    const ViewDesc *__restrict__ views, int nviews, FoveaRows fr, const uint32_t *__restrict__ block_sums,
+    const uint32_t *__restrict__ block_act, int nblocks, int parts, uint32_t *__restrict__ m_dev,
+    unsigned long long *__restrict__ m_total, uint32_t *__restrict__ a_dev, uint32_t *__restrict__ flags,
+    int64_t capacity, int tbits, uint32_t *__restrict__ totals, uint32_t *__restrict__ bkey,
+    uint32_t *__restrict__ brec) {
+    __shared__ uint32_t s_cnt[kBinTiles];
+    __shared__ uint32_t s_wave[4];
+    __shared__ unsigned long long s_tot[16];
+    __shared__ uint32_t s_off[kScanTile];
+    __shared__ uint4 s_r0[kScanTile], s_r1[kScanTile];
+    __shared__ ViewDesc s_views[kMaxViews];
+    // `parts` workgroups share a block of 256 records: each scans it, and takes its share
+    // of the block's keys
+    const int block = (int)blockIdx.x / parts, part = (int)blockIdx.x - block * parts;
+    const int r = block * kScanTile + (int)threadIdx.x, rl = min(r, nrec - 1);
+    const uint32_t c = r < nrec ? count[rl] : 0u;
+    const uint2 rc = rect[rl], pk = rspan[rl];
+    if ((int)threadIdx.x < min(nviews, kMaxViews)) s_views[threadIdx.x] = views[threadIdx.x];
+    uint32_t gbase, abase;
+    if (!block_prefix(block_sums, block_act, nblocks, block, nullptr, nullptr, capacity, m_dev, m_total, a_dev,
+                      flags, true, s_tot, gbase, abase))
+        return;   // overflow: nothing placed
+    uint32_t total;
+    const uint32_t off = block_excl_scan_256(c, s_wave, total);
+    const uint32_t first = gbase + off, v = (uint32_t)rl / (uint32_t)n;
+    if (part == 0 && r < nrec) koff[r] = first;
+    // (every part writes the row tables, as it reads them: the same values)
+    if (c != 0u) write_row_table((uint32_t)r, first, rc, pk, sp, rowtab, n, tile, views, fr);
+    s_off[threadIdx.x] = off;
+    s_r0[threadIdx.x] = make_uint4((uint32_t)r, first, c, pk.x);
+    s_r1[threadIdx.x] = make_uint4(rc.x, rc.y, pk.y, v);
+    // the tiles of the block's views
+    const int v0 = block * kScanTile / n, v1 = min(block * kScanTile + kScanTile - 1, nrec - 1) / n;
+    const int t0 = s_views[v0].tile_off, t1 = s_views[v1].tile_off + s_views[v1].tiles_x * s_views[v1].tiles_y;
+    for (int t = t0 + (int)threadIdx.x; t < t1; t += kScanBlock) s_cnt[t] = 0u;
+    __syncthreads();
+    const uint32_t per = (total + (uint32_t)parts - 1u) / (uint32_t)parts;
+    const uint32_t q0 = min(total, (uint32_t)part * per), q1 = min(total, q0 + per);
+    for (uint32_t q = q0 + threadIdx.x; q < q1; q += kScanBlock) {
+        const int lo = find_record(s_off, q);
+        const uint4 a = s_r0[lo], b = s_r1[lo];
+        uint32_t ty, tx;
+        key_tile(a, b, q - s_off[lo], rowtab, ty, tx);
+        const uint32_t t = (uint32_t)s_views[b.w].tile_off + ty * (uint32_t)s_views[b.w].tiles_x + tx;
+        bkey[gbase + q] = t | (atomicAdd(&s_cnt[t], 1u) << tbits);
+        brec[gbase + q] = a.x;
+    }
+    __syncthreads();
+    for (int t = t0 + (int)threadIdx.x; t < t1; t += kScanBlock) {
+        const uint32_t k = s_cnt[t];
+        if (k) s_cnt[t] = atomicAdd(&totals[t], k);
+    }
+    __syncthreads();
+    for (uint32_t q = q0 + threadIdx.x; q < q1; q += kScanBlock) {   // the thread's own keys again
+        const uint32_t k = bkey[gbase + q];
+        bkey[gbase + q] = k + (s_cnt[k & ((1u << tbits) - 1u)] << tbits);
+    }
+}
+
+// Workgroup 0: the ranges and the compositing order (as k_tile_order); the others: the
+// keys, 1024 at a time.  Each scans the tiles' totals itself (8 a thread).
+__global__ __launch_bounds__(1024) void k_bin_place(const uint32_t *__restrict__ totals, int total_tiles, int tbits,
+                                                    const uint32_t *__restrict__ bkey,
+                                                    const uint32_t *__restrict__ brec,
+                                                    const uint32_t *__restrict__ depth_key,
+                                                    uint32_t *__restrict__ pdepth, uint32_t *__restrict__ prec,
+                                                    uint2 *__restrict__ ranges, uint32_t *__restrict__ order) {
+    constexpr int kPer = kBinTiles / 1024;
+    __shared__ uint32_t s_start[kBinTiles];
+    __shared__ uint32_t s_wave[16], s_cls[64];
+    const int t = (int)threadIdx.x, lane = t & 63, w = t >> 6;
+    uint32_t c[kPer], own = 0u;
+#pragma unroll
+    for (int k = 0; k < kPer; k++) {
+        c[k] = t * kPer + k < total_tiles ? totals[t * kPer + k] : 0u;
+        own += c[k];
+    }
+    const uint32_t inc = wave_incl_scan(own);
+    if (lane == 63) s_wave[w] = inc;
+    if (t < 64) s_cls[t] = 0u;
+    __syncthreads();
+    uint32_t at = inc - own, m = 0u;
+#pragma unroll
+    for (int k = 0; k < 16; k++) {
+        if (k < w) at += s_wave[k];
+        m += s_wave[k];
+    }
+    if (blockIdx.x == 0) {   // a counting sort of the tile ids by descending class of their counts
+        uint32_t cls[kPer];
+        uint64_t peers[kPer];
+#pragma unroll
+        for (int k = 0; k < kPer; k++) {
+            const bool valid = t * kPer + k < total_tiles;
+            if (valid) ranges[t * kPer + k] = make_uint2(at, at + c[k]);
+            at += c[k];
+            cls[k] = c[k] ? 32u - (uint32_t)__clz(c[k]) : 0u;
+            peers[k] = class_peers(cls[k], valid);
+            if (valid && lanes_below(peers[k]) == 0u) atomicAdd(&s_cls[cls[k]], (uint32_t)__popcll(peers[k]));
+        }
+        __syncthreads();
+        if (t < 64) {   // first slot of each class, class 32 first
+            const int k = 32 - lane;
+            const uint32_t x = k >= 0 ? s_cls[k] : 0u, sum = wave_incl_scan(x);
+            if (k >= 0) s_cls[k] = sum - x;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kPer; k++) {
+            const bool valid = t * kPer + k < total_tiles;
+            const uint32_t below = lanes_below(peers[k]);
+            uint32_t start = 0u;
+            if (valid && below == 0u) start = atomicAdd(&s_cls[cls[k]], (uint32_t)__popcll(peers[k]));
+            start = __shfl(start, peers[k] ? __builtin_ctzll(peers[k]) : lane, 64);
+            if (valid) order[start + below] = (uint32_t)(t * kPer + k);
+        }
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; k++) {
+        s_start[t * kPer + k] = at;
+        at += c[k];
+    }
+    __syncthreads();
+    const uint32_t stride = (gridDim.x - 1u) * 1024u;
+    for (uint32_t i = (blockIdx.x - 1u) * 1024u + (uint32_t)t; i < m; i += stride) {
+        const uint32_t k = bkey[i], r = brec[i];
+        const uint32_t pos = s_start[k & ((1u << tbits) - 1u)] + (k >> tbits);
+        pdepth[pos] = depth_key[r];
+        prec[pos] = r;
+    }
+}
+
+// Lane i's value from lane i ^ J.
+template <int J>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x) {
+    if constexpr (J == 1) return dpp_shift_u<0xB1, 0xf>(x);        // quad_perm [1, 0, 3, 2]
+    else if constexpr (J == 2) return dpp_shift_u<0x4E, 0xf>(x);   // quad_perm [2, 3, 0, 1]
+    else if constexpr (J == 8) return dpp_shift_u<0x128, 0xf>(x);  // row_ror:8
+    else if constexpr (J == 32) return (uint32_t)__shfl_xor((int)x, 32, 64);
+    else return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, 0x1F | (J << 10));
+}
+
+template <int K, int J>
+__device__ __forceinline__ uint64_t bitonic_step(uint64_t key, int lane) {
+    const uint64_t other = ((uint64_t)lane_xor<J>((uint32_t)(key >> 32)) << 32) | lane_xor<J>((uint32_t)key);
+    const bool take_min = ((lane & J) == 0) == ((lane & K) == 0);
+    return (other < key) == take_min ? other : key;
+}
+template <int K, int J>
+__device__ __forceinline__ uint64_t bitonic_merge(uint64_t key, int lane) {
+    key = bitonic_step<K, J>(key, lane);
+    if constexpr (J > 1) key = bitonic_merge<K, J / 2>(key, lane);
+    return key;
+}
+// The wave's 64 keys in ascending order.
+__device__ __forceinline__ uint64_t wave_sort(uint64_t key, int lane) {
+    key = bitonic_merge<2, 1>(key, lane);
+    key = bitonic_merge<4, 2>(key, lane);
+    key = bitonic_merge<8, 4>(key, lane);
+    key = bitonic_merge<16, 8>(key, lane);
+    key = bitonic_merge<32, 16>(key, lane);
+    return bitonic_merge<64, 32>(key, lane);
+}
+
+__device__ __forceinline__ uint64_t bin_key(uint32_t depth, uint32_t rec) { return ((uint64_t)depth << 32) | rec; }
+
+// Sorts len <= 1024 PER keys, PER a thread (key e of thread t is number 1024 e + t; past
+// the list, anything): runs of 64 in registers, then pairs of runs merged in place - a
+// key's place in the merged run is its place in its own plus the number of smaller
+// keys in the other, found by binary search.  at: where each key belongs.
+template <int PER>
+__device__ __forceinline__ void bin_merge(uint64_t *s_key, uint64_t (&key)[PER], uint32_t (&at)[PER], uint32_t len) {
+    const uint32_t t = threadIdx.x;
+#pragma unroll
+    for (int e = 0; e < PER; e++) {
+        at[e] = (uint32_t)e * 1024u + t;
+        key[e] = wave_sort(at[e] < len ? key[e] : ~0ull, (int)(t & 63u));
+    }
+    for (uint32_t run = 64u; run < len; run <<= 1) {
+#pragma unroll
+        for (int e = 0; e < PER; e++)
+            if (at[e] < len) s_key[at[e]] = key[e];
+        __syncthreads();
+        uint32_t from[PER], lo[PER], end[PER];
+#pragma unroll
+        for (int e = 0; e < PER; e++) {
+            from[e] = lo[e] = (at[e] & ~(run - 1u)) ^ run;   // the other run
+            end[e] = min(from[e] + run, len);                // (none past the list)
+        }
+        for (uint32_t step = run; step > 0u; step >>= 1)
+#pragma unroll
+            for (int e = 0; e < PER; e++) {
+                const uint32_t mid = lo[e] + step;
+                if (mid <= end[e] && s_key[mid - 1u] < key[e]) lo[e] = mid;
+            }
+#pragma unroll
+        for (int e = 0; e < PER; e++)
+            if (at[e] < len) at[e] = (at[e] & ~run) + (lo[e] - from[e]);
+        __syncthreads();
+    }
+}
+
+// (din, rin) sorted to rout and, with dout, the depths too (in place: yes).
+template <int PER>
+__device__ __forceinline__ void bin_merge_sort(uint64_t *s_key, const uint32_t *din, const uint32_t *rin,
+                                               uint32_t *dout, uint32_t *rout, uint32_t len) {
+    uint64_t key[PER];
+    uint32_t at[PER];
+#pragma unroll
+    for (int e = 0; e < PER; e++) {
+        const uint32_t i = (uint32_t)e * 1024u + threadIdx.x;
+        key[e] = i < len ? bin_key(din[i], rin[i]) : 0ull;
+    }
+    bin_merge<PER>(s_key, key, at, len);
+#pragma unroll
+    for (int e = 0; e < PER; e++)
+        if (at[e] < len) {
+            rout[at[e]] = (uint32_t)key[e];
+            if (dout) dout[at[e]] = (uint32_t)(key[e] >> 32);
+        }
+}
+
+// Pairs of sorted runs of `run` keys merged from (din, rin) to (dout, rout), as above.
+__device__ __forceinline__ void bin_merge_far(const uint32_t *din, const uint32_t *rin, uint32_t *dout,
+                                              uint32_t *rout, uint32_t len, uint32_t run) {
+    constexpr int kPer = 2;
+    for (uint32_t i0 = threadIdx.x; i0 < len; i0 += kPer * 1024u) {
+        uint64_t key[kPer];
+        uint32_t at[kPer], from[kPer], lo[kPer], end[kPer];
+#pragma unroll
+        for (int e = 0; e < kPer; e++) {
+            at[e] = i0 + (uint32_t)e * 1024u;
+            key[e] = at[e] < len ? bin_key(din[at[e]], rin[at[e]]) : 0ull;
+            from[e] = lo[e] = (at[e] & ~(run - 1u)) ^ run;
+            end[e] = min(from[e] + run, len);
+        }
+        for (uint32_t step = run; step > 0u; step >>= 1)
+#pragma unroll
+            for (int e = 0; e < kPer; e++) {
+                const uint32_t mid = lo[e] + step;
+                if (mid <= end[e] && bin_key(din[mid - 1u], rin[mid - 1u]) < key[e]) lo[e] = mid;
+            }
+#pragma unroll
+        for (int e = 0; e < kPer; e++)
+            if (at[e] < len) {
+                const uint32_t pos = (at[e] & ~run) + (lo[e] - from[e]);
+                dout[pos] = (uint32_t)(key[e] >> 32);
+                rout[pos] = (uint32_t)key[e];
+            }
+    }
+    __syncthreads();
+}
+
+// (dep, rec) sorted in runs of kBinSort, which are then merged through memory
+// ((dtmp, rtmp): room for as many); the records end in rec.
+__device__ __forceinline__ void bin_sort_runs(uint64_t *s_key, uint32_t *dep, uint32_t *rec, uint32_t *dtmp,
+                                              uint32_t *rtmp, uint32_t len) {
+    for (uint32_t i = 0u; i < len; i += (uint32_t)kBinSort) {
+        bin_merge_sort<kBinSort / 1024>(s_key, dep + i, rec + i, dep + i, rec + i, min(len - i, (uint32_t)kBinSort));
+        __syncthreads();
+    }
+    uint32_t *din = dep, *rin = rec, *dout = dtmp, *rout = rtmp;
+    for (uint32_t run = (uint32_t)kBinSort; run < len; run <<= 1) {
+        bin_merge_far(din, rin, dout, rout, len, run);
+        uint32_t *d = din, *r = rin;
+        din = dout;
+        rin = rout;
+        dout = d;
+        rout = r;
+    }
+    if (rin != rec)
+        for (uint32_t i = threadIdx.x; i < len; i += 1024u) rec[i] = rin[i];
+    __syncthreads();
+}
+
+// One workgroup per tile, long lists first: its keys sorted by (depth, record), as
+// 64-bit numbers.  A list too long for LDS is first dealt into 256 buckets between
+// splitters drawn from a sorted sample of 1024 of its keys, and then sorted a few
+// buckets at a time.  A bitonic network in LDS, whose every step waits for the one
+// before, took 71 us for three views of 60001 phantom Gaussians (768000 keys, lists
+// of up to 6000), and this 56; for one view of 50000 20 us, and this 12.
+__global__ __launch_bounds__(1024, 8) void k_bin_sort(const uint2 *__restrict__ ranges,
+                                                      const uint32_t *__restrict__ order, uint32_t *pdepth,
+                                                      uint32_t *prec, uint32_t *qdepth, uint32_t *qrec) {
+    __shared__ uint64_t s_key[kBinSort];
+    __shared__ uint64_t s_split[256];
+    __shared__ uint32_t s_end[256], s_wave[4];
+    const uint2 rg = ranges[order[blockIdx.x]];
+    const uint32_t len = rg.y - rg.x, t = threadIdx.x;
+    if (len < 2u) return;
+    uint32_t *rec = prec + rg.x, *dep = pdepth + rg.x, *qr = qrec + rg.x, *qd = qdepth + rg.x;
+    if (len <= 1024u) return bin_merge_sort<1>(s_key, dep, rec, nullptr, rec, len);
+    if (len <= 2048u) return bin_merge_sort<2>(s_key, dep, rec, nullptr, rec, len);
+    if (len <= (uint32_t)kBinSort) return bin_merge_sort<kBinSort / 1024>(s_key, dep, rec, nullptr, rec, len);
+    if (len <= 2u * kBinSort) return bin_sort_runs(s_key, dep, rec, qd, qr, len);
+    {
+        const uint32_t i = (uint32_t)(((uint64_t)t * len) >> 10);
+        uint64_t key[1] = {bin_key(dep[i], rec[i])};
+        uint32_t at[1];
+        bin_merge<1>(s_key, key, at, 1024u);
+        // bucket b: the keys from splitter b - 1 up to splitter b
+        if ((at[0] & 3u) == 0u && at[0] > 0u) s_split[at[0] / 4u - 1u] = key[0];
+        if (t == 0u) s_split[255] = ~0ull;
+        if (t < 256u) s_end[t] = 0u;
+    }
+    __syncthreads();
+    auto bucket = [&](uint64_t key) {
+        uint32_t b = 0u;
+#pragma unroll
+        for (uint32_t step = 128u; step > 0u; step >>= 1)
+            if (s_split[b + step - 1u] <= key) b += step;
+        return b;
+    };
+    for (uint32_t i = t; i < len; i += 1024u) atomicAdd(&s_end[bucket(bin_key(dep[i], rec[i]))], 1u);
+    __syncthreads();
+    {   // the buckets' first places
+        const uint32_t x = t < 256u ? s_end[t] : 0u, inc = wave_incl_scan(x);
+        if (t < 256u && (t & 63u) == 63u) s_wave[t >> 6] = inc;
+        __syncthreads();
+        if (t < 256u) {
+            uint32_t before = inc - x;
+            for (uint32_t k = 0u; k < (t >> 6); k++) before += s_wave[k];
+            s_end[t] = before;
+        }
+        __syncthreads();
+    }
+    for (uint32_t i = t; i < len; i += 1024u) {
+        const uint32_t d = dep[i], r = rec[i];
+        const uint32_t pos = atomicAdd(&s_end[bucket(bin_key(d, r))], 1u);   // ends at the bucket's end
+        qd[pos] = d;
+        qr[pos] = r;
+    }
+    __syncthreads();
+    for (uint32_t b = 0u, from = 0u; b < 256u;) {   // the buckets from `from` that fit together
+        uint32_t to = s_end[b++];
+        while (b < 256u && s_end[b] - from <= (uint32_t)kBinSort) to = s_end[b++];
+        const uint32_t n = to - from;
+        if (n <= (uint32_t)kBinSort) {
+            bin_merge_sort<kBinSort / 1024>(s_key, qd + from, qr + from, nullptr, rec + from, n);
+            __syncthreads();
+        } else {   // one bucket too full
+            bin_sort_runs(s_key, qd + from, qr + from, dep + from, rec + from, n);
+            for (uint32_t i = from + t; i < to; i += 1024u) rec[i] = qr[i];
+            __syncthreads();
+        }
+        from = to;
+    }
+}
+
+}  // namespace
+
+namespace {
+int tile_id_bits(int total_tiles) {
+    int b = 0;
+    while ((1 << b) < total_tiles) b++;
+    return b;
+}
 }  // namespace
 
 int radix_grid_for(int64_t capacity) {
@@ -1086,5 +1487,43 @@ void launch_tile_order(hipStream_t s, const uint2 *ranges, int total_tiles, uint
     k_order_place<<<g, 256, 0, s>>>(ranges, total_tiles, counts, g, order);
 }
 
+// The rule: the counters of a workgroup fit into LDS, each block of records sums its
+// own prefix, and the records are not so many to a tile that the middle tiles' lists
+// are better sorted by the whole device than by a workgroup each.  Phantom Gaussians on
+// 512 x 512 and 256 x 256 pixels, general path to bins: 98 a tile 392 to 357 us, 195 a
+// tile 396 to 386, 256 a tile 508 to 555, 1023 a tile 839 to 999.  On this side of the line:
+// a fit of 1000 on 128 x 128 pixels 130 to 89 us, of 20000 on 512 x 512 220 to 151, of 50000
+// on 1024 x 1024 317 to 241, of 60001 in three views 541 to 508, of 260000 on 1024 x
+// 1024 533 to 455; forward and backward of 262144 on 701 x 533 600 to 327.
+bool binned_lists(int64_t nrec, int64_t total_tiles, int64_t arec_bytes) {
+    static_assert((int64_t)kBinTiles * kOwnPrefixBlocks * kScanTile <= int64_t(1) << 32, "a key holds tile and place");
+    return total_tiles <= kBinTiles && nrec <= (int64_t)kOwnPrefixBlocks * kScanTile &&
+           nrec <= kBinCrowd * total_tiles && total_tiles * 4 <= arec_bytes;
+}
+
+void launch_scan_bin(hipStream_t s, const uint32_t *count, const uint2 *rect, const uint2 *rspan, SplatPtrs sp,
+                     uint32_t *koff, uint2 *rowtab, int nrec, int n, int tile, const ViewDesc *views, int nviews,
+                     const FoveaRows &fr, const uint32_t *block_sums, const uint32_t *block_act, uint32_t *m_dev,
+                     unsigned long long *m_total, uint32_t *a_dev, uint32_t *flags, int64_t capacity,
+                     int total_tiles, uint32_t *totals, uint32_t *bkey, uint32_t *brec) {
+    const int nb = (nrec + kScanTile - 1) / kScanTile;
+    const int parts = std::max(1, std::min(8, 512 / nb));
+    k_scan_bin<<<nb * parts, kScanBlock, 0, s>>>(count, rect, rspan, sp, koff, rowtab, nrec, n, tile, views, nviews,
+                                                 fr, block_sums, block_act, nb, parts, m_dev, m_total, a_dev, flags,
+                                                 capacity, tile_id_bits(total_tiles), totals, bkey, brec);
+}
+
+void launch_bin_place(hipStream_t s, const uint32_t *totals, int total_tiles, int64_t capacity, const uint32_t *bkey,
+                      const uint32_t *brec, const uint32_t *depth_key, uint32_t *pdepth, uint32_t *prec,
+                      uint2 *ranges, uint32_t *order) {
+    const int g = (int)std::max<int64_t>(1, std::min<int64_t>((capacity + 4095) / 4096, 255));
+    k_bin_place<<<1 + g, 1024, 0, s>>>(totals, total_tiles, tile_id_bits(total_tiles), bkey, brec, depth_key, pdepth,
+                                       prec, ranges, order);
+}
+
+void launch_bin_sort(hipStream_t s, const uint2 *ranges, const uint32_t *order, int total_tiles,
+                     uint32_t *pdepth, uint32_t *prec, uint32_t *qdepth, uint32_t *qrec) {
+    k_bin_sort<<<total_tiles, 1024, 0, s>>>(ranges, order, pdepth, prec, qdepth, qrec);
+}
 
 }  // namespace gsf
