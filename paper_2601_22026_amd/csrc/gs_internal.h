@@ -46,8 +46,8 @@ struct ViewDesc {
 // 3e-5 px at 1000 px) would otherwise dominate it.  The conic is stored
 // pre-scaled so that power2 = A2 dx^2 + C2 dy^2 + B2 dx dy = log2(e) * power,
 // i.e. A2 = -log2(e) A / 2, B2 = -log2(e) B, C2 = -log2(e) C / 2; the
-// compositing kernels compare power2 with tau = log2(1 / (255 opacity)), below
-// which alpha < 1/255.
+// compositing kernels compare -power2 with -tau = log2(255 opacity), beyond
+// which alpha < 1/255, by the bits: c holds those of -tau plus one.
 // The splat of a record (record = Gaussian x view) as one 64-byte aligned
 // chunk, the four float4 that staging a key reads: a, b, c and the support
 // ellipse.  A key's staging gathers one chunk instead of a piece of four

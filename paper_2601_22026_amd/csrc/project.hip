@@ -307,11 +307,14 @@ __device__ __forceinline__ uint32_t project_gauss(const Gauss &g, const float *s
         col[ch] = fmaxf(acc + 0.5f, 0.f);
     }
     // conic pre-scaled for a base-2 exponent, and the alpha threshold of the
-    // same exponent: o 2^power2 >= 1/255 where power2 >= tau = -log2(255 o)
+    // same exponent: o 2^power2 >= 1/255 where power2 >= tau = -log2(255 o), kept as
+    // the bits of -tau plus one (zero where nothing reaches it)
+    const float ntau = log2f(255.f * g.o);
+    const float limit = ntau >= 0.f ? __uint_as_float(__float_as_uint(fabsf(ntau)) + 1u) : 0.f;
     *sp.at(r, kRecA) = make_float4((float)(ixd + 0.5 - mxd), (float)(iyd + 0.5 - myd),
                                    (-0.5f * kLog2e) * p.A, -kLog2e * p.B);
     *sp.at(r, kRecB) = make_float4((-0.5f * kLog2e) * p.C, g.o, col[0], col[1]);
-    *sp.at(r, kRecC) = make_float4(col[2], -log2f(255.f * g.o), (float)ixd, (float)iyd);
+    *sp.at(r, kRecC) = make_float4(col[2], limit, (float)ixd, (float)iyd);
     if (empty) {
         rect[r] = make_uint2(0u, 0u);
         rspan[r] = make_uint2(0u, 0u);   // every record: whole 64-byte chunks are written

@@ -41,15 +41,22 @@ namespace {
 constexpr float kLn2 = 0.69314718055994531f;
 
 // Shared by every kernel that walks a tile list so all take identical decisions.
-// a = (hx, hy, A2, B2), b = (C2, opacity, red, green), c = (blue, tau, ix, iy)
+// a = (hx, hy, A2, B2), b = (C2, opacity, red, green), c = (blue, limit, ix, iy)
 // with A2 = -log2(e) A / 2, B2 = -log2(e) B, C2 = -log2(e) C / 2; (x, y) is
 // the integer pixel (as float) and (dx, dy) its centre's offset from the mean.
 __device__ __forceinline__ float splat_dx(float x, float ix, float hx) { return (x - ix) + hx; }
 
-// power2 = A2 dx^2 + B2 dx dy + C2 dy^2, evaluated as dx (A2 dx + B2 dy) + (C2 dy) dy
-// (five operations); every kernel that decides inclusion uses this one form.
-__device__ __forceinline__ float splat_power2(const float4 &a, const float4 &b, float dx, float dy) {
-    return fmaf(dx, fmaf(a.z, dx, a.w * dy), (b.x * dy) * dy);
+// -power2 = -(A2 dx^2 + B2 dx dy + C2 dy^2), evaluated as -(dx (A2 dx + B2 dy) + (C2 dy) dy)
+// (five operations, the signs being modifiers); every kernel that decides inclusion
+// uses this one form.
+__device__ __forceinline__ float splat_fall(const float4 &a, const float4 &b, float dx, float dy) {
+    return fmaf(-dx, fmaf(a.z, dx, a.w * dy), ((-b.x) * dy) * dy);
+}
+// Whether a splat with this fall is included: 0 <= fall <= -tau, one comparison of
+// the bits with the record's limit, the bits of -tau plus one (a negative fall has the
+// sign bit; it is never -0, as (-C2 dy) dy is at least +0).
+__device__ __forceinline__ bool splat_within(float fall, float limit) {
+    return __float_as_uint(fall) < __float_as_uint(limit);
 }
 
 __device__ __forceinline__ bool splat_alpha(const float4 &a, const float4 &b, const float4 &c,
@@ -57,16 +64,16 @@ __device__ __forceinline__ bool splat_alpha(const float4 &a, const float4 &b, co
                                             float &dx, float &dy) {
     dx = splat_dx(x, c.z, a.x);
     dy = splat_dx(y, c.w, a.y);
-    const float power2 = splat_power2(a, b, dx, dy);
-    if (power2 > 0.f || power2 < c.y) return false;
-    ex = __builtin_amdgcn_exp2f(power2);
+    const float fall = splat_fall(a, b, dx, dy);
+    if (!splat_within(fall, c.y)) return false;
+    ex = __builtin_amdgcn_exp2f(-fall);
     ae = b.y * ex;
     alpha = fminf(kAlphaMax, ae);
     return true;
 }
 
-// A record's c = (blue, tau, ix, iy): tau = -log2(255 o) is the alpha
-// threshold of the base-2 exponent, computed once by the projection.  The
+// A record's c = (blue, limit, ix, iy): the limit comes of tau = -log2(255 o), the
+// alpha threshold of the base-2 exponent, computed once by the projection.  The
 // padded half height of the support (where o e^power >= 1/255 can hold) is
 // the ellipse's y extent plus the absolute padding.
 // Half height of the padded ellipse for the quadrant test, with the hardware
@@ -160,7 +167,12 @@ __global__ __launch_bounds__((fwd_threads<T, SPLIT>())) void k_render_fwd(
     constexpr int ROWS = NT / T;
     constexpr int U = 4;   // splats between wave-level completion checks
     static_assert(U == 4, "a group of splat indices is read as one int4");
-    constexpr int kListLen = 64 + U;   // per wave: one 64-splat chunk, padded
+    // AHEAD (split tiles, whose few waves cannot hide the LDS reads): the reads of
+    // a group are issued before the group in front of it is blended, two sets of
+    // registers in turn (4% on one view of 1024^2, 5% on one of 512^2).
+    constexpr bool AHEAD = SPLIT;
+    constexpr int kPad = AHEAD ? 4 * U : U;
+    constexpr int kListLen = 64 + kPad;   // per wave: one 64-splat chunk, padded
     // PREF (a batch no larger than the workgroup): two LDS buffers; the
     // records of the next batch are copied from global memory straight into
     // the other buffer (global_load_lds, no registers; wave w copies entries
@@ -171,7 +183,7 @@ __global__ __launch_bounds__((fwd_threads<T, SPLIT>())) void k_render_fwd(
     // (slope, kw, ws, dyr) at sections 0, 1, 2, 3 of B + 1 entries.  Buffers
     // 0 and 1 are separate arrays, so the compiler sees that reads of one do
     // not wait for copies into the other.  Entry B of a, b, c: an inert splat
-    // (power2 = 0 < tau = +inf: never included) that pads a wave's last
+    // (limit 0: never included) that pads a wave's last
     // group of U.
     // (Entry 0 of each array is unused: a copy addressed at an array's very
     // start loses the alias information that lets reads of the other buffer
@@ -209,11 +221,11 @@ __global__ __launch_bounds__((fwd_threads<T, SPLIT>())) void k_render_fwd(
     if (threadIdx.x == 0) {
         s_buf0[B] = make_float4(0.f, 0.f, 0.f, 0.f);
         s_buf0[SEC + B] = make_float4(0.f, 0.f, 0.f, 0.f);
-        s_buf0[2 * SEC + B] = make_float4(0.f, __builtin_inff(), 0.f, 0.f);
+        s_buf0[2 * SEC + B] = make_float4(0.f, 0.f, 0.f, 0.f);
         if constexpr (PREF) {
             s_buf1[B] = make_float4(0.f, 0.f, 0.f, 0.f);
             s_buf1[SEC + B] = make_float4(0.f, 0.f, 0.f, 0.f);
-            s_buf1[2 * SEC + B] = make_float4(0.f, __builtin_inff(), 0.f, 0.f);
+            s_buf1[2 * SEC + B] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
     }
 
@@ -292,28 +304,34 @@ __global__ __launch_bounds__((fwd_threads<T, SPLIT>())) void k_render_fwd(
             const int cnt = (int)__popcll(m);
             int *list = s_list + wave * kListLen;
             if (meet) list[lanes_below(m)] = jl * (int)sizeof(float4);
-            if (lane < U) list[cnt + lane] = B * (int)sizeof(float4);
-            for (int g = 0; g < cnt; g += U) {
+            if (lane < kPad) list[cnt + lane] = B * (int)sizeof(float4);
+            struct Group {
+                uint32_t bo[U];
+                float4 a[U], b[U], c[U];
+            };
+            auto read_group = [&](const int4 &j4) __attribute__((always_inline)) {
+                Group q;
+                q.bo[0] = (uint32_t)j4.x;
+                q.bo[1] = (uint32_t)j4.y;
+                q.bo[2] = (uint32_t)j4.z;
+                q.bo[3] = (uint32_t)j4.w;
+#pragma unroll
+                for (int u = 0; u < U; u++) {
+                    q.a[u] = *(const float4 *)((const char *)SA + q.bo[u]);
+                    q.b[u] = *(const float4 *)((const char *)SB + q.bo[u]);
+                    q.c[u] = *(const float4 *)((const char *)SC + q.bo[u]);
+                }
+                return q;
+            };
+            auto all_stopped = [&]() __attribute__((always_inline)) {
                 bool all = true;
 #pragma unroll
                 for (int k = 0; k < PPT; k++) all &= !(Tr[k] > 0.f);
-                if (__all(all)) {
-                    done = true;
-                    break;
-                }
-                const int4 j4 = *(const int4 *)(list + g);
-                const uint32_t bo[U] = {(uint32_t)j4.x, (uint32_t)j4.y, (uint32_t)j4.z, (uint32_t)j4.w};
-                // Phase 1: the U splats' alphas are independent of each other and of
-                // the pixel state; computed without branches (skipped splats get
-                // valid = false; every operand is read whatever the outcome).
-                float4 a[U], b[U];
-                float4 c[U];
-#pragma unroll
-                for (int u = 0; u < U; u++) {
-                    a[u] = *(const float4 *)((const char *)SA + bo[u]);
-                    b[u] = *(const float4 *)((const char *)SB + bo[u]);
-                    c[u] = *(const float4 *)((const char *)SC + bo[u]);
-                }
+                return (bool)__all(all);
+            };
+            auto blend = [&](const Group &q) __attribute__((always_inline)) {
+                const uint32_t(&bo)[U] = q.bo;
+                const float4(&a)[U] = q.a, (&b)[U] = q.b, (&c)[U] = q.c;
 #pragma unroll
                 for (int k = 0; k < PPT; k++) {
                     float alpha[U];
@@ -322,32 +340,66 @@ __global__ __launch_bounds__((fwd_threads<T, SPLIT>())) void k_render_fwd(
                     for (int u = 0; u < U; u++) {
                         const float dx = splat_dx(px[k], c[u].z, a[u].x);
                         const float dy = splat_dx(py[k], c[u].w, a[u].y);
-                        const float power2 = splat_power2(a[u], b[u], dx, dy);
-                        valid[u] = !(power2 > 0.f) & !(power2 < c[u].y);
-                        alpha[u] = fminf(kAlphaMax, b[u].y * __builtin_amdgcn_exp2f(power2));
+                        const float fall = splat_fall(a[u], b[u], dx, dy);
+                        valid[u] = splat_within(fall, c[u].y);
+                        alpha[u] = valid[u] ? fminf(kAlphaMax, b[u].y * __builtin_amdgcn_exp2f(-fall)) : 0.f;
                     }
                     // Phase 2: the sequential front-to-back update.  An included
                     // splat performs exactly the float operations of the definition
                     // (Tn = T (1 - alpha), w = alpha T, C += colour w); any other
-                    // gets w = 0, which leaves the (non-negative) colour sums as
-                    // they are bit for bit.
+                    // has alpha 0, or gets w = 0, which leaves T and the
+                    // (non-negative) colour sums as they are bit for bit.  That the
+                    // skipped ones are folded into alpha in phase 1 keeps scalar
+                    // mask operations off the chain from T to T (5 to 7% of the
+                    // kernel, 11% where a wave has a SIMD for itself; what bounds it is the
+                    // 24 vector operations a splat and pixel, 72 cycles).  Branches
+                    // around the update instead of selects: 5 to 10% slower; a form
+                    // without the stop test for groups in which no pixel stops: 4 to 7%.
 #pragma unroll
                     for (int u = 0; u < U; u++) {
                         // A stopped pixel holds -T < 0, so its Tn < 0 < kTStop: it is
                         // never included, and -|T| keeps it stopped.  A running pixel
                         // stops where Tn < kTStop and then holds -T.
                         const float Tn = Tr[k] * (1.f - alpha[u]);
-                        const bool inc = valid[u] && !(Tn < kTStop);
-                        const bool stop = valid[u] && !inc;
-                        if (MODE == 2 && inc)
+                        const bool on = !(Tn < kTStop);
+                        if (MODE == 2 && valid[u] && on)
                             tstore[(size_t)(bs + bo[u] / (uint32_t)sizeof(float4)) * (T * T) + pix[k]] = Tr[k];
-                        const float w = (inc ? alpha[u] : 0.f) * Tr[k];
+                        const float w = (on ? alpha[u] : 0.f) * Tr[k];
                         cr[k] = fmaf(b[u].z, w, cr[k]);
                         cg[k] = fmaf(b[u].w, w, cg[k]);
                         cb[k] = fmaf(c[u].x, w, cb[k]);
-                        Tr[k] = inc ? Tn : (stop ? -fabsf(Tr[k]) : Tr[k]);
-                        lastb[k] = inc ? bo[u] : lastb[k];
+                        Tr[k] = on ? Tn : -fabsf(Tr[k]);
+                        lastb[k] = valid[u] && on ? bo[u] : lastb[k];
                     }
+                }
+            };
+            if constexpr (AHEAD) {
+                Group q0 = read_group(*(const int4 *)list), q1;
+                int4 j = *(const int4 *)(list + U);
+                for (int g = 0; g < cnt; g += 2 * U) {
+                    if (all_stopped()) {
+                        done = true;
+                        break;
+                    }
+                    q1 = read_group(j);
+                    j = *(const int4 *)(list + g + 2 * U);
+                    blend(q0);
+                    if (g + U >= cnt) break;
+                    if (all_stopped()) {
+                        done = true;
+                        break;
+                    }
+                    q0 = read_group(j);
+                    j = *(const int4 *)(list + g + 3 * U);
+                    blend(q1);
+                }
+            } else {
+                for (int g = 0; g < cnt; g += U) {
+                    if (all_stopped()) {
+                        done = true;
+                        break;
+                    }
+                    blend(read_group(*(const int4 *)(list + g)));
                 }
             }
         }
@@ -562,9 +614,8 @@ __device__ __forceinline__ void render_bwd_unit(
     row[64 + lane] = g1;
     row[128 + lane] = g2;
     if (lane == 0) sh.nmax[wave] = qmax;
-    if (tid < 6) {   // the inert splat of both buffers: power2 = 0 < tau = +inf, never included
-        sh.rec[tid & 1][tid >> 1][kAdjChunk] =
-            make_float4(0.f, tid >> 1 == 2 ? __builtin_inff() : 0.f, 0.f, 0.f);
+    if (tid < 6) {   // the inert splat of both buffers: limit 0, never included
+        sh.rec[tid & 1][tid >> 1][kAdjChunk] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     __syncthreads();
     uint32_t nmax = 0u;
@@ -688,11 +739,11 @@ __device__ __forceinline__ void render_bwd_unit(
                     const float4 c = *(const float4 *)((const char *)sh.rec[0][kRecC] + bo[u]);
                     const float dx = splat_dx(px, c.z, a.x);
                     const float dy = splat_dx(py, c.w, a.y);
-                    const float power2 = splat_power2(a, b, dx, dy);
-                    const bool inc = (bo[u] < lim) & !(power2 > 0.f) & !(power2 < c.y);
+                    const float fall = splat_fall(a, b, dx, dy);
+                    const bool inc = (bo[u] < lim) & splat_within(fall, c.y);
                     in4[u] = inc;
                     if (__builtin_amdgcn_ballot_w64(inc)) took |= 1u << (h + u);
-                    const float ex = __builtin_amdgcn_exp2f(inc ? power2 : -__builtin_inff());
+                    const float ex = __builtin_amdgcn_exp2f(-(inc ? fall : __builtin_inff()));
                     const float ae = b.y * ex;
                     al[u] = fminf(kAlphaMax, ae);
                     inv[u] = __builtin_amdgcn_rcpf(1.f - al[u]);   // alpha <= 0.99
@@ -997,12 +1048,12 @@ __device__ __forceinline__ void render_bwd_tile(
                 // with zero sums, without a select per quantity.
                 const float dx = splat_dx(px[k], c.z, a.x);
                 const float dy = splat_dx(py[k], c.w, a.y);
-                const float power2 = splat_power2(a, b, dx, dy);
-                const bool inc = (pos < nc[k]) & !(power2 > 0.f) & !(power2 < c.y);
+                const float fall = splat_fall(a, b, dx, dy);
+                const bool inc = (pos < nc[k]) & splat_within(fall, c.y);
                 // no pixel of the block takes the splat: every lane would add
                 // zeros and keep its state (wave-uniform)
                 if (!__any(inc)) continue;
-                const float ex = __builtin_amdgcn_exp2f(MODE == 2 || inc ? power2 : -__builtin_inff());
+                const float ex = __builtin_amdgcn_exp2f(-(MODE == 2 || inc ? fall : __builtin_inff()));
                 const float ae = b.y * ex;
                 const float alpha = CLAMP ? fminf(kAlphaMax, ae) : ae;
                 const float inv = __builtin_amdgcn_rcpf(1.f - alpha);   // alpha <= 0.99
