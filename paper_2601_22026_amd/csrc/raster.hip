@@ -1034,6 +1034,18 @@ __device__ __forceinline__ void render_bwd_tile(
             const float4 a = sh.rec[0][j], b = sh.rec[1][j], c = sh.rec[2][j];
             // the splat's quadrant mask, wave-uniform: tested in scalar registers
             const uint32_t qm = (uint32_t)__builtin_amdgcn_readlane((int)qmask, j);
+            // the offsets and the terms in y, of the two columns and two rows of
+            // quadrants (once instead of per quadrant: 1920 -> 1883 us on sixteen
+            // views of 1920^2)
+            constexpr int NC = PPT == 4 ? 2 : 1;
+            float dxc[NC], dyr[NC], wy[NC], vy[NC];
+#pragma unroll
+            for (int i = 0; i < NC; i++) {
+                dxc[i] = splat_dx(px[i], c.z, a.x);
+                dyr[i] = splat_dx(py[2 * i], c.w, a.y);
+                wy[i] = a.w * dyr[i];
+                vy[i] = ((-b.x) * dyr[i]) * dyr[i];
+            }
             float acc[9];
             // (-0 is the exact identity of addition, so the first term needs no add)
 #pragma unroll
@@ -1046,9 +1058,8 @@ __device__ __forceinline__ void render_bwd_tile(
                 // below 1/255) takes power -inf instead, so exp2 = 0, alpha = 0, 1 /
                 // (1 - alpha) = 1 and its state passes through unchanged bit for bit
                 // with zero sums, without a select per quantity.
-                const float dx = splat_dx(px[k], c.z, a.x);
-                const float dy = splat_dx(py[k], c.w, a.y);
-                const float fall = splat_fall(a, b, dx, dy);
+                const float dx = dxc[k % NC], dy = dyr[k / NC];
+                const float fall = fmaf(-dx, fmaf(a.z, dx, wy[k / NC]), vy[k / NC]);   // splat_fall
                 const bool inc = (pos < nc[k]) & splat_within(fall, c.y);
                 // no pixel of the block takes the splat: every lane would add
                 // zeros and keep its state (wave-uniform)
