@@ -442,7 +442,7 @@ __global__ __launch_bounds__(256) void k_block_totals(const uint32_t *__restrict
 // count of its records to block_sums[b], the first level of the scan that
 // places the keys.
 template <int DEG>
-__global__ __launch_bounds__(256) void k_project_fwd(const float *__restrict__ P, int n, int nrec,
+__global__ __launch_bounds__(256) void k_project_fwd(const float *__restrict__ P, int n, int nrec, int nviews,
                                                      const gsf_camera *__restrict__ cams,
                                                      const ViewDesc *__restrict__ views, int tile,
                                                      SplatPtrs sp, uint32_t *__restrict__ depth_key,
@@ -455,8 +455,16 @@ __global__ __launch_bounds__(256) void k_project_fwd(const float *__restrict__ P
                                                      uint32_t *__restrict__ block_act,
                                                      uint32_t *__restrict__ clear, int nclear) {
     __shared__ uint32_t s_w[4], s_a[4];
-    const int r = blockIdx.x * 256 + (int)threadIdx.x;
-    for (int i = r; i < nclear; i += (int)gridDim.x * 256) clear[i] = 0u;
+    for (int i = blockIdx.x * 256 + (int)threadIdx.x; i < nclear; i += (int)gridDim.x * 256) clear[i] = 0u;
+    // The block of records: the views' blocks of the same Gaussians are eight
+    // workgroups apart, that is one after the other on the same XCD, so that the
+    // parameters are still in its L2 for the second and later views (a million
+    // Gaussians of third degree in two views: 130 -> 108 us; 200000 in eight: 77 -> 72).
+    const int nb = (nrec + 255) / 256, per = (nb + nviews - 1) / nviews;
+    const int g = (int)blockIdx.x / (8 * nviews), l = (int)blockIdx.x - g * 8 * nviews;
+    const int c0 = g * 8 + (l & 7), block = (l >> 3) * per + c0;
+    if (c0 >= per || block >= nb) return;
+    const int r = block * 256 + (int)threadIdx.x;
     uint32_t c = r < nrec ? project_record<DEG>(P, n, r, cams, views, tile, sp, depth_key, rect, count,
                                                 rspan, cull_gaze, cull_radius, fr)
                           : 0u;
@@ -469,8 +477,8 @@ __global__ __launch_bounds__(256) void k_project_fwd(const float *__restrict__ P
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        block_sums[blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
-        block_act[blockIdx.x] = s_a[0] + s_a[1] + s_a[2] + s_a[3];
+        block_sums[block] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+        block_act[block] = s_a[0] + s_a[1] + s_a[2] + s_a[3];
     }
 }
 
@@ -687,7 +695,8 @@ void launch_project_fwd(hipStream_t s, const float *P, int n, int nviews, int de
                         uint32_t *block_sums,
                         uint32_t *block_act, uint32_t *clear, int nclear) {
     const int nrec = n * nviews;
-    const dim3 grid((nrec + 255) / 256), block(256);
+    const int per = ((nrec + 255) / 256 + nviews - 1) / nviews;   // blocks of records a view
+    const dim3 grid((per + 7) / 8 * 8 * nviews), block(256);
     if (deg <= 1 && nviews > 1) {   // one thread per Gaussian for all views, then the block totals
         const dim3 ggrid((n + 255) / 256);
         if (deg == 0)
@@ -700,10 +709,10 @@ void launch_project_fwd(hipStream_t s, const float *P, int n, int nviews, int de
         return;
     }
     switch (deg) {
-    case 0: k_project_fwd<0><<<grid, block, 0, s>>>(P, n, nrec, cams, views, tile, sp, depth_key, rect, count, rspan, cull_gaze, cull_radius, fr, block_sums, block_act, clear, nclear); break;
-    case 1: k_project_fwd<1><<<grid, block, 0, s>>>(P, n, nrec, cams, views, tile, sp, depth_key, rect, count, rspan, cull_gaze, cull_radius, fr, block_sums, block_act, clear, nclear); break;
-    case 2: k_project_fwd<2><<<grid, block, 0, s>>>(P, n, nrec, cams, views, tile, sp, depth_key, rect, count, rspan, cull_gaze, cull_radius, fr, block_sums, block_act, clear, nclear); break;
-    default: k_project_fwd<3><<<grid, block, 0, s>>>(P, n, nrec, cams, views, tile, sp, depth_key, rect, count, rspan, cull_gaze, cull_radius, fr, block_sums, block_act, clear, nclear); break;
+    case 0: k_project_fwd<0><<<grid, block, 0, s>>>(P, n, nrec, nviews, cams, views, tile, sp, depth_key, rect, count, rspan, cull_gaze, cull_radius, fr, block_sums, block_act, clear, nclear); break;
+    case 1: k_project_fwd<1><<<grid, block, 0, s>>>(P, n, nrec, nviews, cams, views, tile, sp, depth_key, rect, count, rspan, cull_gaze, cull_radius, fr, block_sums, block_act, clear, nclear); break;
+    case 2: k_project_fwd<2><<<grid, block, 0, s>>>(P, n, nrec, nviews, cams, views, tile, sp, depth_key, rect, count, rspan, cull_gaze, cull_radius, fr, block_sums, block_act, clear, nclear); break;
+    default: k_project_fwd<3><<<grid, block, 0, s>>>(P, n, nrec, nviews, cams, views, tile, sp, depth_key, rect, count, rspan, cull_gaze, cull_radius, fr, block_sums, block_act, clear, nclear); break;
     }
 }
 
