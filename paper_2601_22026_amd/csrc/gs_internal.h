@@ -534,6 +534,19 @@ void launch_tile_order(hipStream_t s, const uint2 *ranges, int total_tiles, uint
 int order_groups(int64_t total_tiles);
 
 // Everything the compositing kernels share.
+// The final reduction of a loss launch: its per-workgroup partial sums and where the
+// mean goes (null partial: none).
+struct LossTail {
+    const float *partial = nullptr;
+    int nparts = 0;
+    const uint32_t *mask_count = nullptr;   // entries of the mean, on the device, or
+    uint32_t count_host = 0;                //   on the host when mask_count is null
+    float *loss = nullptr;
+    uint32_t *flags = nullptr;
+    int32_t *step_inc = nullptr;            // optimiser step counter to advance (may be null)
+    bool accumulate = false;
+};
+
 struct RenderArgs {
     int tile = 16, batch = 128, total_tiles = 0, nviews = 1, nrec = 0;
     int t_mode = 0;                       // 0 recompute, 1 checkpointed, 2 stored transmittance
@@ -560,6 +573,7 @@ struct RenderArgs {
     // global tile ids, or (tm.gaze, a fovea-culled forward) the compact
     // fovea-box ids of the sort keys
     TileMap tm{};
+    LossTail tail{};                      // adjoint: a loss's reduction left to its launch
 };
 
 // Front-to-back compositing of all tiles of all views.
@@ -587,14 +601,16 @@ int loss_partials(int64_t total_pix);
 // that meet the fovea; nviews * box^2 <= total_pix); dl elsewhere is not written.
 // RGBA targets (tgt_planes 4): the target colour is composited over bg
 // ([V][3], nullable = black) and, with alpha_term, alpha is a fourth L1 channel.
-void launch_loss_l1(hipStream_t s, const float *rgba, const float *target, const float *gaze,
+LossTail launch_loss_l1(hipStream_t s, const float *rgba, const float *target, const float *gaze,
                     float radius_frac, const ViewDesc *views, int nviews, int64_t total_pix,
                     float *dl, float *partial, uint32_t *mask_count, float *loss, uint32_t *flags,
                     int32_t *step_inc, int box, int tile, int tgt_planes, bool alpha_term,
-                    const float *bg, uint32_t norm_count, bool accumulate, int max_height);
+                    const float *bg, uint32_t norm_count, bool accumulate, int max_height,
+                        bool defer = false);
 // norm_count > 0: the mean divides by it (entries over all plans of a multi-plan
 // loss) instead of the plan's own masked count; accumulate: loss[0] += the share.
-// max_height: the tallest view's height.
+// max_height: the tallest view's height.  defer: the final reduction is left to the
+// adjoint's launch (RenderArgs::tail = the value returned).
 // The masked entry count alone (gaze required) into mask_count[0].
 void launch_loss_count(hipStream_t s, const float *gaze, float radius_frac, const ViewDesc *views,
                        int nviews, int max_height, int box, int tile, uint32_t channels,

@@ -517,28 +517,31 @@ gsf_status enqueue_forward(gsf_plan *p, const float *params, int64_t n, const gs
 // cull: visit only the pixels of the tiles that meet each view's fovea (gaze
 // required) - a window of box x box pixels per view, when that is smaller.
 // tgt_planes 4: RGBA targets composited over bg (nullable) with an alpha term
-// when alpha_term.
+// when alpha_term.  tail (nullable): takes the loss's final reduction, for the
+// adjoint's launch to do.
 gsf_status enqueue_loss(gsf_plan *p, const float *rgba, const float *target, const float *gaze,
                         float radius_frac, float *loss, float *dl, int32_t *step_inc,
                         bool cull = false, int tgt_planes = 3, bool alpha_term = false,
                         const float *bg = nullptr, uint32_t norm_count = 0u,
-                        bool accumulate = false) {
+                        bool accumulate = false, LossTail *tail = nullptr) {
     const int box = cull && gaze ? fovea_box(p, radius_frac) : 0;
     StageTimer t(p, GSF_STAGE_LOSS);
-    launch_loss_l1(p->ctx->stream, rgba, target, gaze, radius_frac, p->b.views, p->V,
+    const LossTail lt = launch_loss_l1(p->ctx->stream, rgba, target, gaze, radius_frac, p->b.views, p->V,
                    p->total_pix, dl, p->b.loss_partial, p->b.mask_count, loss, p->b.flags,
                    step_inc, box, p->tile, tgt_planes, alpha_term, bg, norm_count, accumulate,
-                   max_height(p));
+                   max_height(p), tail != nullptr);
+    if (tail) *tail = lt;
     GSF_LAUNCHED(p->ctx);
     return GSF_OK;
 }
 
 gsf_status enqueue_backward(gsf_plan *p, const float *params, int64_t n, const gsf_camera *cams,
                             const float *dl, float *grads, const float *bg = nullptr,
-                            bool accumulate = false) {
+                            bool accumulate = false, const LossTail &tail = {}) {
     hipStream_t s = p->ctx->stream;
     RenderArgs ra = render_args(p, cams, n);
     ra.bg = bg;
+    ra.tail = tail;
     {   // per-key screen-space gradients
         StageTimer t(p, GSF_STAGE_RENDER_BWD);
         launch_render_bwd(s, ra, dl);
@@ -613,11 +616,14 @@ gsf_status enqueue_step(gsf_plan *p, const gsf_step_args *a, bool with_adam = tr
     gsf_status st = enqueue_forward(p, a->params, a->n, a->cams, a->rgba, &overflow,
                                     cull ? a->gaze_px : nullptr, a->mask_radius_frac, bg);
     if (st != GSF_OK) return st;
-    // the loss reduction also advances the Adam step counter of this step
+    // the loss reduction, which also advances the Adam step counter of this step, is
+    // left to the adjoint's launch
+    LossTail tail;
     st = enqueue_loss(p, a->rgba, a->target_rgb, a->gaze_px, a->mask_radius_frac, a->loss,
-                      a->dl_drgba, a->step_dev, cull, a->alpha_loss ? 4 : 3, a->alpha_loss != 0, bg);
+                      a->dl_drgba, a->step_dev, cull, a->alpha_loss ? 4 : 3, a->alpha_loss != 0, bg,
+                      0u, false, &tail);
     if (st != GSF_OK) return st;
-    st = enqueue_backward(p, a->params, a->n, a->cams, a->dl_drgba, a->grads, bg);
+    st = enqueue_backward(p, a->params, a->n, a->cams, a->dl_drgba, a->grads, bg, false, tail);
     if (st != GSF_OK) return st;
     if (!with_adam) return overflow ? fail(p->ctx, GSF_E_CAPACITY, "key capacity exceeded") : GSF_OK;
     const int C = planes_of(p->deg);

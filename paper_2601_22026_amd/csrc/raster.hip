@@ -492,6 +492,53 @@ __global__ __launch_bounds__((fwd_threads<T, SPLIT>())) void k_render_fwd(
     }
 }
 
+// ---- the loss's final reduction ---------------------------------------------------
+//
+// Sum of the loss's partials in a fixed order (deterministic) -> loss; optionally
+// advances the optimiser step counter (the fit step's Adam runs after it).  The order
+// is that of 1024 threads whatever the workgroup: each of its NW waves takes the
+// places of 16 / NW waves in turn.  A call of the loss alone runs it as a kernel of one
+// workgroup; in a fit step it is one more workgroup of the adjoint, which needs none
+// of it, and costs no launch (the smallest step 88 us to 85.5).
+constexpr int kTailWaves = 16;
+
+template <int NW>
+__device__ __forceinline__ void loss_tail(const LossTail &lt, float *s_part) {
+    const int lane = (int)(threadIdx.x & 63);
+    const int n4 = lt.nparts / 4;
+    for (int w = (int)(threadIdx.x >> 6); w < kTailWaves; w += NW) {
+        // four partials per thread and step (16-byte loads; the tail one by one),
+        // in four sums
+        const int t = 64 * w + lane;
+        float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+        for (int k = t; k < n4; k += 64 * kTailWaves) {
+            const float4 v = reinterpret_cast<const float4 *>(lt.partial)[k];
+            s0 += v.x;
+            s1 += v.y;
+            s2 += v.z;
+            s3 += v.w;
+        }
+        for (int k = 4 * n4 + t; k < lt.nparts; k += 64 * kTailWaves) s0 += lt.partial[k];
+        float s = (s0 + s1) + (s2 + s3);
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);   // same tree on every lane
+        if (lane == 0) s_part[w] = s;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float tot = 0.f;
+#pragma unroll
+        for (int w = 0; w < kTailWaves; w++) tot += s_part[w];
+        const uint32_t cnt = lt.mask_count ? *lt.mask_count : lt.count_host;
+        const float L = tot / (float)max(cnt, 1u);
+        lt.loss[0] = lt.accumulate ? lt.loss[0] + L : L;   // accumulate: one share of a multi-plan loss
+        if (!isfinite(L)) atomicOr(lt.flags, GSF_FLAG_NONFINITE);
+        // a step whose keys overflowed the capacity is not counted (its Adam
+        // update is skipped too, so it can be repeated after a re-plan)
+        if (lt.step_inc && !(*lt.flags & GSF_FLAG_CAPACITY)) lt.step_inc[0] = lt.step_inc[0] + 1;
+    }
+}
+
 // ---- adjoint ---------------------------------------------------------------------
 //
 // One wave per 8 x 8 block of the tile's pixels (T / 8 squared waves a
@@ -1200,9 +1247,14 @@ __global__ __launch_bounds__((adj_threads<T, WIDE>()), WIDE && T == 16 ? 4 : 1) 
     const ViewDesc *__restrict__ views, int nviews, const gsf_camera *__restrict__ cams,
     const float *__restrict__ tfinal, const uint32_t *__restrict__ ncontrib,
     const float *__restrict__ tstore, const float *__restrict__ bg, const float *__restrict__ dl,
-    KeyPlace kp, TileMap tm) {
+    KeyPlace kp, TileMap tm, LossTail lt) {
     __shared__ typename AdjForm<T, WIDE>::Shared sh;
-    const uint32_t ti = order[blockIdx.x];
+    const uint32_t tail = lt.partial ? 1u : 0u;   // workgroup 0 finishes the loss
+    if (blockIdx.x < tail) {
+        loss_tail<adj_threads<T, WIDE>() / 64>(lt, reinterpret_cast<float *>(&sh));
+        return;
+    }
+    const uint32_t ti = order[blockIdx.x - tail];
     const uint2 rg = ranges[ti];
     // a tile without keys passes no gradient (and a fovea-culled step's tiles
     // away from the fovea hold no pixel state to read)
@@ -1229,12 +1281,17 @@ __global__ __launch_bounds__((adj_threads<T, WIDE>()), WIDE && T == 16 ? 4 : 1) 
     const ViewDesc *__restrict__ views, int nviews, const gsf_camera *__restrict__ cams,
     const float *__restrict__ tfinal, const uint32_t *__restrict__ ncontrib,
     const float4 *__restrict__ fstate, const float4 *__restrict__ ckpt,
-    const float *__restrict__ bg, const float *__restrict__ dl, KeyPlace kp, TileMap tm) {
+    const float *__restrict__ bg, const float *__restrict__ dl, KeyPlace kp, TileMap tm, LossTail lt) {
     __shared__ typename AdjForm<T, WIDE>::Shared sh;
+    const uint32_t tail = lt.partial ? 1u : 0u;   // workgroup 0 finishes the loss
+    if (blockIdx.x < tail) {
+        loss_tail<adj_threads<T, WIDE>() / 64>(lt, reinterpret_cast<float *>(&sh));
+        return;
+    }
     const uint32_t m = m_dev ? *m_dev : m_host;
     const uint32_t n_ids = m / B + (uint32_t)total_tiles;
     const int lane = (int)(threadIdx.x & 63);
-    for (uint32_t id = blockIdx.x; id < n_ids; id += gridDim.x) {   // one trip when the grid covers n_ids
+    for (uint32_t id = blockIdx.x - tail; id < n_ids; id += gridDim.x - tail) {   // one trip when the grid covers n_ids
         // largest tile t with first id floor(start_t / B) + t <= id: in [lo, lo + len)
         int lo = 0, len = total_tiles;
         while (len > 1) {   // wave-uniform
@@ -1471,8 +1528,8 @@ __global__ __launch_bounds__(kLossBlock) void k_loss_count(const float *__restri
 // Per-pixel L1 terms and sign gradient, and one partial sum per workgroup.
 // The count of masked entries comes from mask_count (device) or count_host.
 // (A last-workgroup-done reduction would need an agent-scope release fence per
-// workgroup, which writes back the L2 just filled with dL/dRGBA; a second
-// one-workgroup kernel is cheaper.)
+// workgroup, which writes back the L2 just filled with dL/dRGBA; the sum is left
+// to a workgroup of a later kernel.)
 __global__ __launch_bounds__(kLossBlock) void k_loss_l1(
     const float *__restrict__ rgba, const float *__restrict__ target, const float *__restrict__ gaze,
     float radius_frac, const ViewDesc *__restrict__ views, int nviews, int64_t total_pix, int box,
@@ -1576,43 +1633,10 @@ __global__ __launch_bounds__(kLossBlock) void k_loss_l1(
     }
 }
 
-// Sum of the partials in a fixed order (deterministic) -> loss; optionally
-// advances the optimiser step counter (the fit step's Adam runs after it).
-__global__ __launch_bounds__(1024) void k_loss_final(const float *__restrict__ partial, int nparts,
-                                                     const uint32_t *__restrict__ mask_count,
-                                                     uint32_t count_host, float *__restrict__ loss,
-                                                     uint32_t *__restrict__ flags,
-                                                     int32_t *__restrict__ step_inc, bool accumulate) {
-    __shared__ float s_part[16];
-    // four partials per thread and step (16-byte loads; the tail one by one),
-    // in four sums: a fixed order, so the loss is deterministic
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    const int n4 = nparts / 4;
-    for (int k = threadIdx.x; k < n4; k += 1024) {
-        const float4 v = reinterpret_cast<const float4 *>(partial)[k];
-        s0 += v.x;
-        s1 += v.y;
-        s2 += v.z;
-        s3 += v.w;
-    }
-    for (int k = 4 * n4 + (int)threadIdx.x; k < nparts; k += 1024) s0 += partial[k];
-    float s = (s0 + s1) + (s2 + s3);
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);   // same tree on every lane
-    if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float tot = 0.f;
-#pragma unroll
-        for (int w = 0; w < 16; w++) tot += s_part[w];
-        const uint32_t cnt = mask_count ? *mask_count : count_host;
-        const float L = tot / (float)max(cnt, 1u);
-        loss[0] = accumulate ? loss[0] + L : L;   // accumulate: one share of a multi-plan loss
-        if (!isfinite(L)) atomicOr(flags, GSF_FLAG_NONFINITE);
-        // a step whose keys overflowed the capacity is not counted (its Adam
-        // update is skipped too, so it can be repeated after a re-plan)
-        if (step_inc && !(*flags & GSF_FLAG_CAPACITY)) step_inc[0] = step_inc[0] + 1;
-    }
+// One workgroup for the loss's final reduction (loss_tail).
+__global__ __launch_bounds__(1024) void k_loss_final(LossTail lt) {
+    __shared__ float s_part[kTailWaves];
+    loss_tail<kTailWaves>(lt, s_part);
 }
 
 // Per-view random background: SplitMix64 (Steele, Lea and Flood, OOPSLA 2014)
@@ -1683,18 +1707,19 @@ void render_fwd_tb(hipStream_t s, const RenderArgs &a, float *out) {
 template <int T, bool WIDE>
 void render_bwd_tw(hipStream_t s, const RenderArgs &a, const float *dl) {
     constexpr int NT = adj_threads<T, WIDE>();
+    const int tail = a.tail.partial ? 1 : 0;
     if (a.t_mode == 1)
-        k_render_bwd_ckpt<T, WIDE><<<a.bwd_grid, NT, 0, s>>>(
+        k_render_bwd_ckpt<T, WIDE><<<a.bwd_grid + tail, NT, 0, s>>>(
             a.ranges, a.total_tiles, (uint32_t)a.batch, a.m_dev, a.m_host, a.vals, a.sp, a.views, a.nviews,
-            a.cams, a.tfinal, a.ncontrib, a.fstate, a.ckpt, a.bg, dl, a.kp, a.tm);
+            a.cams, a.tfinal, a.ncontrib, a.fstate, a.ckpt, a.bg, dl, a.kp, a.tm, a.tail);
     else if (a.t_mode == 2)
-        k_render_bwd<T, 2, WIDE><<<a.total_tiles, NT, 0, s>>>(a.order, a.ranges, a.vals, a.sp, a.views,
+        k_render_bwd<T, 2, WIDE><<<a.total_tiles + tail, NT, 0, s>>>(a.order, a.ranges, a.vals, a.sp, a.views,
                                                              a.nviews, a.cams, a.tfinal, a.ncontrib,
-                                                             a.tstore, a.bg, dl, a.kp, a.tm);
+                                                             a.tstore, a.bg, dl, a.kp, a.tm, a.tail);
     else
-        k_render_bwd<T, 0, WIDE><<<a.total_tiles, NT, 0, s>>>(a.order, a.ranges, a.vals, a.sp, a.views,
+        k_render_bwd<T, 0, WIDE><<<a.total_tiles + tail, NT, 0, s>>>(a.order, a.ranges, a.vals, a.sp, a.views,
                                                              a.nviews, a.cams, a.tfinal, a.ncontrib,
-                                                             nullptr, a.bg, dl, a.kp, a.tm);
+                                                             nullptr, a.bg, dl, a.kp, a.tm, a.tail);
 }
 
 template <int T>
@@ -1765,11 +1790,11 @@ int loss_launch_blocks(int64_t total_pix, int nviews, int box) {
     return box ? nviews * loss_blocks_per_view(box) : (int)((total_pix + kLossSpan - 1) / kLossSpan);
 }
 
-void launch_loss_l1(hipStream_t s, const float *rgba, const float *target, const float *gaze,
+LossTail launch_loss_l1(hipStream_t s, const float *rgba, const float *target, const float *gaze,
                     float radius_frac, const ViewDesc *views, int nviews, int64_t total_pix,
                     float *dl, float *partial, uint32_t *mask_count, float *loss, uint32_t *flags,
                     int32_t *step_inc, int box, int tile, int tgt_planes, bool alpha_term,
-                    const float *bg, uint32_t norm_count, bool accumulate, int max_height) {
+                    const float *bg, uint32_t norm_count, bool accumulate, int max_height, bool defer) {
     if (!gaze) box = 0;
     const uint32_t channels = alpha_term ? 4u : 3u;
     const int nb = loss_launch_blocks(total_pix, nviews, box);
@@ -1780,7 +1805,9 @@ void launch_loss_l1(hipStream_t s, const float *rgba, const float *target, const
     const uint32_t cnt = norm_count ? norm_count : (uint32_t)(channels * total_pix);
     k_loss_l1<<<nb, kLossBlock, 0, s>>>(rgba, target, gaze, radius_frac, views, nviews, total_pix, box,
                                         tile, tgt_planes, alpha_term, bg, mc, cnt, dl, partial);
-    k_loss_final<<<1, 1024, 0, s>>>(partial, nb, mc, cnt, loss, flags, step_inc, accumulate);
+    const LossTail lt{partial, nb, mc, cnt, loss, flags, step_inc, accumulate};
+    if (!defer) k_loss_final<<<1, 64 * kTailWaves, 0, s>>>(lt);
+    return lt;
 }
 
 void launch_loss_count(hipStream_t s, const float *gaze, float radius_frac, const ViewDesc *views,
