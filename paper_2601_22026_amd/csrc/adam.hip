@@ -6,7 +6,8 @@
 // Training"); zeroing m, v and the step counter is that restart.  The step
 // counter lives in device memory so a captured step graph can be replayed.
 // In the fused step the loss reduction advances it; a standalone call
-// advances it with a one-thread kernel first.
+// advances it with a one-thread kernel first.  (At SH degrees 0 and 1 the fused step's
+// update is part of the kernel that finishes the gradient, k_project_bwd.)
 #include "gs_internal.h"
 
 namespace gsf {
@@ -23,15 +24,6 @@ __device__ __forceinline__ float seg_lr(const SegTable &seg, int64_t e) {
     return lr;
 }
 
-__device__ __forceinline__ void adam_one(float &p, float g, float &m, float &v, float lr, float b1,
-                                         float b2, float ibc1, float ibc2, float eps) {
-    m = fmaf(b1, m, (1.f - b1) * g);
-    v = fmaf(b2, v, (1.f - b2) * (g * g));
-    const float mh = m * ibc1;
-    const float vh = v * ibc2;
-    p -= lr * mh / (sqrtf(vh) + eps);
-}
-
 // 4 elements per thread; segment boundaries may fall anywhere.
 __global__ __launch_bounds__(256) void k_adam(float *__restrict__ p, const float *__restrict__ g,
                                               float *__restrict__ m, float *__restrict__ v, int64_t n,
@@ -39,9 +31,8 @@ __global__ __launch_bounds__(256) void k_adam(float *__restrict__ p, const float
                                               const int32_t *__restrict__ step,
                                               const uint32_t *__restrict__ skip) {
     if (skip && (*skip & GSF_FLAG_CAPACITY)) return;   // the step's keys overflowed
-    const float t = (float)step[0];
-    const float ibc1 = 1.f / (1.f - powf(b1, t));
-    const float ibc2 = 1.f / (1.f - powf(b2, t));
+    const AdamRate rate = adam_rate(b1, b2, step);
+    const float ibc1 = rate.ibc1, ibc2 = rate.ibc2;
     const int64_t n4 = n / 4;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n4; q += stride) {
@@ -92,17 +83,16 @@ __global__ __launch_bounds__(256) void k_adam_masked(float *__restrict__ p,
                                                      const int32_t *__restrict__ step,
                                                      const uint32_t *__restrict__ skip) {
     if (skip && (*skip & GSF_FLAG_CAPACITY)) return;   // the step's keys overflowed
-    const float t = (float)step[0];
-    const float ibc1 = 1.f / (1.f - powf(b1, t));
-    const float ibc2 = 1.f / (1.f - powf(b2, t));
+    const AdamRate rate = adam_rate(b1, b2, step);
+    const float ibc1 = rate.ibc1, ibc2 = rate.ibc2;
     const int plane = blockIdx.y;
-    const float rate = lr.lr[plane];
+    const float plane_lr = lr.lr[plane];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         if (!vis[i]) continue;
         const int64_t e = plane * n + i;
         float pe = p[e], me = m[e], ve = v[e];
-        adam_one(pe, g[e], me, ve, rate, b1, b2, ibc1, ibc2, eps);
+        adam_one(pe, g[e], me, ve, plane_lr, b1, b2, ibc1, ibc2, eps);
         p[e] = pe;
         m[e] = me;
         v[e] = ve;

@@ -75,6 +75,32 @@ struct PlaneLr {
     float lr[kMaxPlanes];
 };
 
+// The Adam update of a fit step on planar [planes][n] state (null p: none).
+struct AdamStep {
+    float *p = nullptr, *m = nullptr, *v = nullptr;
+    float b1 = 0.f, b2 = 0.f, eps = 0.f;
+    const int32_t *step = nullptr;    // the step's number, already advanced
+    const uint32_t *skip = nullptr;   // flags: no update after GSF_FLAG_CAPACITY
+    uint8_t *vis = nullptr;           // given: only the Gaussians that touched a tile, noted here
+};
+
+// Bias corrections of the step, and the update of one element.
+struct AdamRate {
+    float ibc1, ibc2;
+};
+__device__ __forceinline__ AdamRate adam_rate(float b1, float b2, const int32_t *step) {
+    const float t = (float)step[0];
+    return {1.f / (1.f - powf(b1, t)), 1.f / (1.f - powf(b2, t))};
+}
+__device__ __forceinline__ void adam_one(float &p, float g, float &m, float &v, float lr, float b1,
+                                         float b2, float ibc1, float ibc2, float eps) {
+    m = fmaf(b1, m, (1.f - b1) * g);
+    v = fmaf(b2, v, (1.f - b2) * (g * g));
+    const float mh = m * ibc1;
+    const float vh = v * ibc2;
+    p -= lr * mh / (sqrtf(vh) + eps);
+}
+
 // Support ellipse of a record for the tile lists, as the constants of its
 // row-wise x extent: for a row offset d from the mean the ellipse (quadratic
 // form <= Kp = 2 ln(255 o) (1 + kBoxRel)^2, covariance Sigma' = [sa sb; sb sc])
@@ -440,10 +466,11 @@ void launch_fovea_rows(hipStream_t s, const float *gaze, float radius_frac, cons
 // the way; for degrees 2-3, whose larger state leaves no registers for the
 // sum, read from g2d, which launch_grad_sum must have written.
 bool project_bwd_sums_keys(int deg);
-// accumulate: grads += the gradient (else grads = it).
+// accumulate: grads += the gradient (else grads = it).  ad (degrees 0-1; P = ad.p,
+// accumulate false): the Adam update of every Gaussian too, plane c at lr.lr[c].
 void launch_project_bwd(hipStream_t s, const float *P, int n, int nviews, int deg,
                         const gsf_camera *cams, const KeyPlace &kp, const float *g2d, float *grads,
-                        bool accumulate = false);
+                        bool accumulate = false, const AdamStep &ad = {}, const PlaneLr &lr = {});
 
 // Record-order exclusive scan of the per-record tile counts: koff[r] (record
 // r's gradient slots, its keys in record order), the row tables of the boxes

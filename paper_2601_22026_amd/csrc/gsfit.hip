@@ -537,7 +537,8 @@ gsf_status enqueue_loss(gsf_plan *p, const float *rgba, const float *target, con
 
 gsf_status enqueue_backward(gsf_plan *p, const float *params, int64_t n, const gsf_camera *cams,
                             const float *dl, float *grads, const float *bg = nullptr,
-                            bool accumulate = false, const LossTail &tail = {}) {
+                            bool accumulate = false, const LossTail &tail = {},
+                            const AdamStep &adam = {}, const PlaneLr &lr = {}) {
     hipStream_t s = p->ctx->stream;
     RenderArgs ra = render_args(p, cams, n);
     ra.bg = bg;
@@ -554,7 +555,8 @@ gsf_status enqueue_backward(gsf_plan *p, const float *params, int64_t n, const g
     GSF_LAUNCHED(p->ctx);
     {   // the chain rule to the parameters (summing the per-key terms itself for SH 0-1)
         StageTimer t(p, GSF_STAGE_PROJECT_BWD);
-        launch_project_bwd(s, params, (int)n, p->V, p->deg, cams, ra.kp, p->b.g2d, grads, accumulate);
+        launch_project_bwd(s, params, (int)n, p->V, p->deg, cams, ra.kp, p->b.g2d, grads, accumulate,
+                           adam, lr);
     }
     GSF_LAUNCHED(p->ctx);
     return GSF_OK;
@@ -623,10 +625,9 @@ gsf_status enqueue_step(gsf_plan *p, const gsf_step_args *a, bool with_adam = tr
                       a->dl_drgba, a->step_dev, cull, a->alpha_loss ? 4 : 3, a->alpha_loss != 0, bg,
                       0u, false, &tail);
     if (st != GSF_OK) return st;
-    st = enqueue_backward(p, a->params, a->n, a->cams, a->dl_drgba, a->grads, bg, false, tail);
-    if (st != GSF_OK) return st;
-    if (!with_adam) return overflow ? fail(p->ctx, GSF_E_CAPACITY, "key capacity exceeded") : GSF_OK;
     const int C = planes_of(p->deg);
+    PlaneLr lr{};
+    for (int c = 0; c < C; c++) lr.lr[c] = a->seg_lr[c];
     std::vector<int64_t> off(C + 1);
     for (int c = 0; c <= C; c++) off[c] = (int64_t)c * a->n;
     // merge equal neighbouring planes into segments (at most 16)
@@ -640,12 +641,31 @@ gsf_status enqueue_step(gsf_plan *p, const gsf_step_args *a, bool with_adam = tr
     }
     so.push_back(off[C]);
     SegTable seg;
-    st = make_segments(p->ctx, off[C], so.data(), sl.data(), (int32_t)sl.size(), &seg);
+    const gsf_status seg_st =
+        make_segments(p->ctx, off[C], so.data(), sl.data(), (int32_t)sl.size(), &seg);
+    // SH degrees 0-1: the kernel that finishes the gradient updates the parameters
+    AdamStep adam;
+    if (with_adam && seg_st == GSF_OK && project_bwd_sums_keys(p->deg)) {
+        adam.p = a->params;
+        adam.m = a->adam_m;
+        adam.v = a->adam_v;
+        adam.b1 = a->beta1;
+        adam.b2 = a->beta2;
+        adam.eps = a->eps;
+        adam.step = a->step_dev;
+        adam.skip = p->b.flags;
+        adam.vis = a->masked_adam ? p->b.vis : nullptr;
+    }
+    st = enqueue_backward(p, a->params, a->n, a->cams, a->dl_drgba, a->grads, bg, false, tail, adam, lr);
     if (st != GSF_OK) return st;
+    if (!with_adam) return overflow ? fail(p->ctx, GSF_E_CAPACITY, "key capacity exceeded") : GSF_OK;
+    if (seg_st != GSF_OK) return seg_st;
+    if (adam.p) {
+        StageTimer t(p, GSF_STAGE_ADAM);   // done by launch_project_bwd
+        return overflow ? fail(p->ctx, GSF_E_CAPACITY, "key capacity exceeded") : GSF_OK;
+    }
     if (a->masked_adam) {   // only the Gaussians that touched a tile in some view
         StageTimer t(p, GSF_STAGE_ADAM);
-        PlaneLr lr{};
-        for (int c = 0; c < C; c++) lr.lr[c] = a->seg_lr[c];
         launch_visible(p->ctx->stream, p->b.count, (int)a->n, p->V, p->b.vis);
         launch_adam_masked(p->ctx->stream, a->params, a->grads, a->adam_m, a->adam_v, a->n, C, lr,
                            p->b.vis, a->beta1, a->beta2, a->eps, a->step_dev, false, p->b.flags);
