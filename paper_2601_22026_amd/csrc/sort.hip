@@ -982,7 +982,7 @@ __global__ __launch_bounds__(256) void k_order_place(const uint2 *__restrict__ r
 // The general path's two radix sorts take up to 24 launches, and at about 4.7 us each they
 // are most of the time that a plan of few records spends before compositing.  Where
 // the tiles' counters fit into LDS three launches do the same:
-// (k_scan_bin 8 to 20 us, k_bin_place 6 to 10, k_bin_sort 5 to 56 at the sizes below; what
+// (k_scan_bin 8 to 20 us, k_bin_place 6 to 10, k_bin_sort 5 to 36 at the sizes below; what
 // bounds them is latency, and the longest list.)
 //   k_scan_bin   the record scan, and every record's keys in record order, each with
 //                its tile and its place within the tile's list: one workgroup counts in
@@ -1165,6 +1165,16 @@ __device__ __forceinline__ uint64_t wave_sort(uint64_t key, int lane) {
     return bitonic_merge<64, 32>(key, lane);
 }
 
+// The wave's 128 keys in ascending order: 0..63 in a, 64..127 in b.
+__device__ __forceinline__ void wave_sort_pair(uint64_t &a, uint64_t &b, int lane) {
+    a = wave_sort(a, lane);
+    b = wave_sort(b, lane);
+    const uint64_t r = ((uint64_t)(uint32_t)__shfl((int)(b >> 32), 63 - lane, 64) << 32) |
+                       (uint32_t)__shfl((int)b, 63 - lane, 64);
+    b = bitonic_merge<64, 32>(a < r ? r : a, lane);
+    a = bitonic_merge<64, 32>(a < r ? a : r, lane);
+}
+
 __device__ __forceinline__ uint64_t bin_key(uint32_t depth, uint32_t rec) { return ((uint64_t)depth << 32) | rec; }
 
 // Sorts len <= 1024 PER keys, PER a thread (key e of thread t is number 1024 e + t; past
@@ -1277,25 +1287,30 @@ __device__ __forceinline__ void bin_sort_runs(uint64_t *s_key, uint32_t *dep, ui
 }
 
 // One workgroup per tile, long lists first: its keys sorted by (depth, record), as
-// 64-bit numbers.  A list too long for LDS is first dealt into 256 buckets between
-// splitters drawn from a sorted sample of 1024 of its keys, and then sorted a few
-// buckets at a time.  A bitonic network in LDS, whose every step waits for the one
-// before, took 71 us for three views of 60001 phantom Gaussians (768000 keys, lists
-// of up to 6000), and this 56; for one view of 50000 20 us, and this 12.
+// 64-bit numbers.  A list of more than kBinMerge keys is first dealt into 256 buckets
+// between splitters drawn from a sorted sample of 1024 of its keys.  Up to kBinDeal
+// keys nearly every bucket holds at most 128, which one wave sorts in registers: what
+// the merging of runs costs is its binary searches in LDS (12 reads a key and round,
+// 24 us for 4096 keys), and a bucket is found by 8.  Longer lists sort a few buckets
+// at a time by merging.  Three views of 60001 phantom Gaussians (768000 keys, lists of
+// up to 6000): 57 us where lists up to 8192 are merged too, 34 here; for one view of
+// 50000, whose lists are shorter, 12 both ways.  (The short path is marked as the
+// likely one: without, one view of 512^2 lost 0.3%.)
+constexpr uint32_t kBinMerge = 2048u;
+constexpr uint32_t kBinDeal = 8192u;
+
 __global__ __launch_bounds__(1024, 8) void k_bin_sort(const uint2 *__restrict__ ranges,
                                                       const uint32_t *__restrict__ order, uint32_t *pdepth,
                                                       uint32_t *prec, uint32_t *qdepth, uint32_t *qrec) {
     __shared__ uint64_t s_key[kBinSort];
     __shared__ uint64_t s_split[256];
-    __shared__ uint32_t s_end[256], s_wave[4];
+    __shared__ uint32_t s_end[256], s_wave[4], s_full;
     const uint2 rg = ranges[order[blockIdx.x]];
     const uint32_t len = rg.y - rg.x, t = threadIdx.x;
     if (len < 2u) return;
     uint32_t *rec = prec + rg.x, *dep = pdepth + rg.x, *qr = qrec + rg.x, *qd = qdepth + rg.x;
-    if (len <= 1024u) return bin_merge_sort<1>(s_key, dep, rec, nullptr, rec, len);
-    if (len <= 2048u) return bin_merge_sort<2>(s_key, dep, rec, nullptr, rec, len);
-    if (len <= (uint32_t)kBinSort) return bin_merge_sort<kBinSort / 1024>(s_key, dep, rec, nullptr, rec, len);
-    if (len <= 2u * kBinSort) return bin_sort_runs(s_key, dep, rec, qd, qr, len);
+    if (__builtin_expect(len <= 1024u, 1)) return bin_merge_sort<1>(s_key, dep, rec, nullptr, rec, len);
+    if (len <= kBinMerge) return bin_merge_sort<2>(s_key, dep, rec, nullptr, rec, len);
     {
         const uint32_t i = (uint32_t)(((uint64_t)t * len) >> 10);
         uint64_t key[1] = {bin_key(dep[i], rec[i])};
@@ -1304,6 +1319,7 @@ __global__ __launch_bounds__(1024, 8) void k_bin_sort(const uint2 *__restrict__ 
         // bucket b: the keys from splitter b - 1 up to splitter b
         if ((at[0] & 3u) == 0u && at[0] > 0u) s_split[at[0] / 4u - 1u] = key[0];
         if (t == 0u) s_split[255] = ~0ull;
+        if (t == 0u) s_full = 0u;
         if (t < 256u) s_end[t] = 0u;
     }
     __syncthreads();
@@ -1314,9 +1330,7 @@ __global__ __launch_bounds__(1024, 8) void k_bin_sort(const uint2 *__restrict__ 
             if (s_split[b + step - 1u] <= key) b += step;
         return b;
     };
-    for (uint32_t i = t; i < len; i += 1024u) atomicAdd(&s_end[bucket(bin_key(dep[i], rec[i]))], 1u);
-    __syncthreads();
-    {   // the buckets' first places
+    auto starts = [&]() {   // the buckets' counts become their first places
         const uint32_t x = t < 256u ? s_end[t] : 0u, inc = wave_incl_scan(x);
         if (t < 256u && (t & 63u) == 63u) s_wave[t >> 6] = inc;
         __syncthreads();
@@ -1326,7 +1340,63 @@ __global__ __launch_bounds__(1024, 8) void k_bin_sort(const uint2 *__restrict__ 
             s_end[t] = before;
         }
         __syncthreads();
+    };
+    if (len <= kBinDeal) {
+        constexpr int kPer = (int)(kBinDeal / 1024u);
+        uint32_t at[kPer];   // a key's bucket and its place there
+#pragma unroll
+        for (int e = 0; e < kPer; e++) {
+            const uint32_t i = (uint32_t)e * 1024u + t;
+            if (i >= len) continue;
+            const uint32_t b = bucket(bin_key(dep[i], rec[i]));
+            at[e] = b << 16 | atomicAdd(&s_end[b], 1u);
+        }
+        __syncthreads();
+        starts();
+#pragma unroll
+        for (int e = 0; e < kPer; e++) {
+            const uint32_t i = (uint32_t)e * 1024u + t;
+            if (i >= len) continue;
+            const uint32_t pos = s_end[at[e] >> 16] + (at[e] & 0xFFFFu);
+            qd[pos] = dep[i];
+            qr[pos] = rec[i];
+        }
+        __syncthreads();
+        const uint32_t lane = t & 63u;
+        for (uint32_t b = t >> 6; b < 256u; b += 16u) {   // a wave's buckets
+            const uint32_t from = s_end[b], n = (b < 255u ? s_end[b + 1u] : len) - from;
+            if (n > 128u) {
+                if (lane == 0u) s_full = 1u;
+                continue;
+            }
+            uint64_t k0 = lane < n ? bin_key(qd[from + lane], qr[from + lane]) : ~0ull;
+            if (n <= 64u) {
+                k0 = wave_sort(k0, (int)lane);
+            } else {
+                uint64_t k1 = lane + 64u < n ? bin_key(qd[from + 64u + lane], qr[from + 64u + lane]) : ~0ull;
+                wave_sort_pair(k0, k1, (int)lane);
+                if (lane + 64u < n) rec[from + 64u + lane] = (uint32_t)k1;
+            }
+            if (lane < n) rec[from + lane] = (uint32_t)k0;
+        }
+        __syncthreads();
+        if (s_full == 0u) return;
+        for (uint32_t b = 0u; b < 256u; b++) {   // the buckets too full for a wave
+            const uint32_t from = s_end[b], n = (b < 255u ? s_end[b + 1u] : len) - from;
+            if (n <= 128u) continue;
+            if (n <= (uint32_t)kBinSort) {
+                bin_merge_sort<kBinSort / 1024>(s_key, qd + from, qr + from, nullptr, rec + from, n);
+            } else {
+                bin_sort_runs(s_key, qd + from, qr + from, dep + from, rec + from, n);
+                for (uint32_t i = from + t; i < from + n; i += 1024u) rec[i] = qr[i];
+            }
+            __syncthreads();
+        }
+        return;
     }
+    for (uint32_t i = t; i < len; i += 1024u) atomicAdd(&s_end[bucket(bin_key(dep[i], rec[i]))], 1u);
+    __syncthreads();
+    starts();
     for (uint32_t i = t; i < len; i += 1024u) {
         const uint32_t d = dep[i], r = rec[i];
         const uint32_t pos = atomicAdd(&s_end[bucket(bin_key(d, r))], 1u);   // ends at the bucket's end

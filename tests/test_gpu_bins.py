@@ -78,6 +78,18 @@ def test_list_lengths(ctx, n):
     log(f"[bins] {n} Gaussians, longest list {longest}")
 
 
+@pytest.mark.parametrize("n,every", [(2304, 2), (4096, 4), (6144, 6), (8192, 8)])
+def test_sample_that_misleads(ctx, n, every):
+    """One tile whose every second (fourth, ...) record, those a sample taken at equal
+    steps finds, lies in front of all others: one bucket holds most of the list."""
+    P = _crowd(n, n)
+    P[0:2] = P[0:2] * 0.01 + 0.05
+    P[2] += np.where(np.arange(n) % every == 0, -0.5, 0.5)
+    sc = GpuScene(ctx, P, [synth.axis_camera(256, 384)])
+    sc.forward()
+    log(f"[bins] {n} Gaussians, every {every}th in front, longest list {_check(sc, 16)}")
+
+
 @pytest.mark.parametrize("tile", [8, 16, 32])
 def test_views_and_boxes(ctx, tile):
     P = synth.with_near_splats(synth.random_gaussians(300, seed=12), 8, seed=12)
