@@ -33,11 +33,10 @@ struct gsf_ctx {
     std::string err;
     unsigned long long *warp_scratch = nullptr;   // device address of the no-allocation z-buffer
     hipError_t warp_scratch_err = hipSuccess;
-    // small device scratch of the calls that read a volume (volume_scratch): the
-    // stream it was last used on, and the event that use ended with
+    // small device scratch of the calls that read a volume (volume_scratch), and the
+    // event its last use ended with
     VolumeScratch vol_scratch;
     hipEvent_t vol_event = nullptr;
-    hipStream_t vol_stream = nullptr;
     bool vol_used = false;
 };
 
@@ -164,7 +163,8 @@ bool capturing(hipStream_t s) {
 }
 
 // The context's volume scratch, for work about to be enqueued on its stream; the work
-// of an earlier call on another stream is waited for first.  Empty under capture,
+// of an earlier call is waited for first (a stream handle does not tell whether it was on
+// this stream: a new stream can have a destroyed one's handle).  Empty under capture,
 // where the graph could run beside a later call: a march then skips nothing (and the
 // seeding, which synchronises, is refused).  volume_scratch_done follows the work.
 VolumeScratch volume_scratch(gsf_ctx *ctx) {
@@ -190,8 +190,7 @@ VolumeScratch volume_scratch(gsf_ctx *ctx) {
         ctx->vol_scratch = {p, (unsigned long long *)h};
         ctx->vol_event = e;
     }
-    if (ctx->vol_used && ctx->vol_stream != ctx->stream &&
-        hipStreamWaitEvent(ctx->stream, ctx->vol_event, 0) != hipSuccess) {
+    if (ctx->vol_used && hipStreamWaitEvent(ctx->stream, ctx->vol_event, 0) != hipSuccess) {
         (void)hipGetLastError();
         return {};
     }
@@ -200,7 +199,6 @@ VolumeScratch volume_scratch(gsf_ctx *ctx) {
 
 gsf_status volume_scratch_done(gsf_ctx *ctx, const VolumeScratch &vs) {
     if (!vs.device) return GSF_OK;
-    ctx->vol_stream = ctx->stream;
     ctx->vol_used = true;
     GSF_HIP(ctx, hipEventRecord(ctx->vol_event, ctx->stream));
     return GSF_OK;
