@@ -552,14 +552,18 @@ __device__ __forceinline__ void loss_tail(const LossTail &lt, float *s_part) {
 //   sum wT {dL/dR, dL/dG, dL/dB}
 // whose right-hand factors do not depend on the splat.  Eight splats' te and wT
 // rows (16 x 64, through LDS) times that 64 x 9 matrix (in registers, laid out
-// once per unit) are sixteen v_mfma_f32_16x16x4_f32 in full FP32.  When a chunk
+// once per unit) are sixteen v_mfma_f64_16x16x4_f64.  When a chunk
 // is done the blocks' sums are moved from their centres to each splat's mean and
 // added in the order of the blocks: no atomics, the same bits in every run.
-// (gfx950 issues no VALU work of other waves under an FP32 matrix instruction, 32
-// cycles each, so the products cost throughput: this form is for plans where the
-// length of the lists, not issue, sets the time.  One view of 128^2 with 1,000
-// Gaussians 71 -> 25 us, of 701 x 533 with 30,000 188 -> 72 us; on sixteen views
-// of 1920^2 it takes 2800 us where one wave per tile takes 1910.)
+// The products are in 64 bits because of that move: where a narrow splat lies off the
+// centre, its sums about the centre are tens of times those about the mean, and FP32
+// products left up to 2.4 times the error in the gradient that sums about the mean
+// have (6,548 Gaussians on 447 x 99: 1.05e-6 of its norm against 4.3e-7; now 4.9e-7).
+// They cost half the rate: an FP32 form took 5 to 13% less time for the whole step.
+// (No VALU work of other waves issues under these instructions, 64 cycles each,
+// so this form is for plans where the length of the lists, not issue, sets the time:
+// fit step of 1,000 Gaussians on 128^2 132 us to 100, forward and backward of 30,011
+// on 701 x 533 358 to 179.)
 constexpr int kAdjChunk = 64;    // records staged at a time
 constexpr int kAdjGroup = 8;     // splats per matrix product (two rows each)
 constexpr int kAdjRow = 68;      // row stride, floats: 16-byte reads of 16 rows fall in distinct banks
@@ -569,6 +573,7 @@ template <int T>
 constexpr int adj_waves() { return (T / 8) * (T / 8); }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 template <int T>
 struct AdjShared {
@@ -576,7 +581,7 @@ struct AdjShared {
     float4 rec[2][4][kAdjSec];            // two chunks' records by section (a, b, c, ellipse)
     uint2 key[2][3][kAdjChunk];           // their boxes, row spans, first key positions
     alignas(16) float row[NW][2 * kAdjGroup * kAdjRow];
-    float sum[NW][kAdjChunk * 9];         // per splat of the chunk: the block's nine sums
+    double sum[NW][kAdjChunk * 9];        // per splat of the chunk: the block's nine sums
     uint64_t hit[NW];                     // splats of the chunk with sums
     alignas(16) int list[NW][kAdjChunk + kAdjGroup];
     uint32_t nmax[NW];
@@ -597,6 +602,7 @@ __device__ __forceinline__ void render_bwd_unit(
     const float4 *__restrict__ fstate, const float4 *__restrict__ ckpt,
     const float *__restrict__ tstore, const float *__restrict__ bg, const float *__restrict__ dl,
     const KeyPlace &kp, AdjShared<T> &sh) {
+    static_assert(T > 8, "an 8-pixel tile is one block");
     constexpr bool CKPT = MODE == 1;
     constexpr int NW = adj_waves<T>(), NT = 64 * NW;
     constexpr int PARTS = NT >= 256 ? 1 : 256 / NT;   // 16-byte record pieces a thread stages per chunk
@@ -751,7 +757,7 @@ __device__ __forceinline__ void render_bwd_unit(
         const int base = buf * (int)sizeof(sh.rec[0]);
         const uint32_t off = cs - rg.x;   // list position of the chunk's first record
         bool meet = lane < nb && off + (uint32_t)lane < qmax;
-        if (T > 8 && meet) {
+        if (meet) {
             const float4 e0 = sh.rec[buf][kRecEll][lane], a0 = SA[lane], c0 = SC[lane];
             const Ellipse e{e0.x, e0.y, e0.z, e0.w, quad_half_height(e0), a0.x, a0.y, (int)c0.z, (int)c0.w};
             meet = quad_meets(e, bx, by);
@@ -812,25 +818,25 @@ __device__ __forceinline__ void render_bwd_unit(
                 }
             }
             __builtin_amdgcn_wave_barrier();
-            f32x4 D = {0.f, 0.f, 0.f, 0.f};
+            f64x4 D = {0.0, 0.0, 0.0, 0.0};
             if (took) {
                 f32x4 av[4];
 #pragma unroll
                 for (int i = 0; i < 4; i++) av[i] = *(const f32x4 *)(row + (lane & 15) * kAdjRow + 16 * kq + 4 * i);
 #pragma unroll
                 for (int m = 0; m < 16; m++)
-                    D = __builtin_amdgcn_mfma_f32_16x16x4f32(av[m >> 2][m & 3], bq[m], D, 0, 0, 0);
+                    D = __builtin_amdgcn_mfma_f64_16x16x4f64((double)av[m >> 2][m & 3], (double)bq[m], D, 0, 0, 0);
             }
-            // lane (j, k) holds column j of rows 4 k .. 4 k + 3: te and wT of the
-            // group's splats 2 k and 2 k + 1.  A splat no pixel included has zeros.
-            if (j < 9) {
-                const int2 jo = *(const int2 *)(list + g + 2 * kq);
-                const float s0 = j < 6 ? D[0] : D[1], s1 = j < 6 ? D[2] : D[3];
-                float *const S = sh.sum[wave] + j;
-                if (g + 2 * kq < cnt)
-                    S[((jo.x - base) >> 4) * 9] = (took >> (2 * kq)) & 1u ? s0 : 0.f;
-                if (g + 2 * kq + 1 < cnt)
-                    S[((jo.y - base) >> 4) * 9] = (took >> (2 * kq + 1)) & 1u ? s1 : 0.f;
+            // lane (j, k) holds column j of rows k, k + 4, k + 8 and k + 12: te (k even) or
+            // wT of the group's splats k / 2, + 2, + 4 and + 6.  A splat no pixel included
+            // has zeros.
+            if ((kq & 1) ? j >= 6 && j < 9 : j < 6) {
+                double *const S = sh.sum[wave] + j;
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    const int e = (kq >> 1) + 2 * r;
+                    if (g + e < cnt) S[((list[g + e] - base) >> 4) * 9] = (took >> e) & 1u ? D[r] : 0.0;
+                }
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -847,30 +853,35 @@ __device__ __forceinline__ void render_bwd_unit(
             const float4 a = SA[e], b = SB[e], c = SC[e];
             float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
             if (part < 3) {
-                float sx = 0.f, sy = 0.f, sxx = 0.f, sxy = 0.f, syy = 0.f, s0 = 0.f, r0 = 0.f, r1 = 0.f, r2 = 0.f;
+                // in 64 bits, as the sums about the centre of a block cancel where a small
+                // splat lies off it
+                double dx = 0.0, dy = 0.0, dxx = 0.0, dxy = 0.0, dyy = 0.0;
+                float s0 = 0.f, r0 = 0.f, r1 = 0.f, r2 = 0.f;
 #pragma unroll
                 for (int w = 0; w < NW; w++) {
                     if (!((sh.hit[w] >> e) & 1ull)) continue;
-                    const float *M = sh.sum[w] + 9 * e;
+                    const double *M = sh.sum[w] + 9 * e;
                     if (part == 2) {
-                        r2 += M[8];
+                        r2 += (float)M[8];
                         continue;
                     }
                     // the block centre's offset from the mean
-                    const float ey = splat_dx((float)(ty * T + (w / QX) * 8) + 3.5f, c.w, a.y);
+                    const double ey = (double)((float)(ty * T + (w / QX) * 8) + 3.5f - c.w) + (double)a.y;
                     if (part == 1) {
-                        syy += fmaf(ey, fmaf(ey, M[0], 2.f * M[2]), M[5]);
-                        s0 += M[0];
-                        r0 += M[6];
-                        r1 += M[7];
+                        dyy += fma(ey, fma(ey, M[0], 2.0 * M[2]), M[5]);
+                        s0 += (float)M[0];
+                        r0 += (float)M[6];
+                        r1 += (float)M[7];
                         continue;
                     }
-                    const float ex = splat_dx((float)(tx * T + (w % QX) * 8) + 3.5f, c.z, a.x);
-                    sx += fmaf(ex, M[0], M[1]);
-                    sy += fmaf(ey, M[0], M[2]);
-                    sxx += fmaf(ex, fmaf(ex, M[0], 2.f * M[1]), M[3]);
-                    sxy += fmaf(ex, fmaf(ey, M[0], M[2]), fmaf(ey, M[1], M[4]));
+                    const double ex = (double)((float)(tx * T + (w % QX) * 8) + 3.5f - c.z) + (double)a.x;
+                    const double m0 = M[0], m1 = M[1], m2 = M[2];
+                    dx += fma(ex, m0, m1);
+                    dy += fma(ey, m0, m2);
+                    dxx += fma(ex, fma(ex, m0, 2.0 * m1), M[3]);
+                    dxy += fma(ex, fma(ey, m0, m2), fma(ey, m1, M[4]));
                 }
+                const float sx = (float)dx, sy = (float)dy, sxx = (float)dxx, sxy = (float)dxy, syy = (float)dyy;
                 const float o = b.y;   // te sums -> dL/dpower sums
                 if (part == 0)
                     out = make_float4(-kLn2 * o * (2.f * a.z * sx + a.w * sy),
@@ -1732,20 +1743,23 @@ void render_fwd_t(hipStream_t s, const RenderArgs &a, float *out) {
 // The adjoint takes one wave per 8 x 8 block while the plan has at most
 // kWideTilesPerCu (checkpointed mode, whose units cut the lists short:
 // kWideCkptTilesPerCu) 16-pixel tiles' worth of tiles per compute unit, one wave per
-// tile above.  Checkpointed, one 512^2 view (1,024 tiles) 40 against 64 us, three
-// views of 0.17-0.48 Mpix (3,800 tiles) 212 against 147, one of 1024^2 (4,096) 107
-// against 80; recomputed, 701 x 533 (1,496) 72 against 153, the three views 537
-// against 1086, 8-pixel tiles on 1024^2 175 against 219, eight views of 0.25-4 Mpix
-// (42,000) 1399 against 835.
-constexpr int kWideTilesPerCu = 16, kWideCkptTilesPerCu = 8;
+// tile above.  Fit steps with blocks against tiles, 20,000 phantom and 30,000 random
+// Gaussians: recomputed on 512^2 276 : 471 and 199 : 283 us, on 800^2 222 : 346 and
+// 230 : 258, on 1024^2 218 : 312 and 285 : 270; checkpointed on 256^2 224 : 237 and 181 :
+// 180, on 384^2 170 : 185 and 176 : 171, on 512^2 171 : 170 and 203 : 176.  An 8-pixel
+// tile is one block and has one wave in both forms: there the products only cost.
+constexpr int kWideTilesPerCu = 16, kWideCkptTilesPerCu = 3;
 
 template <int T>
 void render_bwd_t(hipStream_t s, const RenderArgs &a, const float *dl) {
     const int per_cu = a.t_mode == 1 ? kWideCkptTilesPerCu : kWideTilesPerCu;
-    if ((int64_t)a.total_tiles * (T * T) <= (int64_t)per_cu * 256 * a.cus)
-        render_bwd_tw<T, true>(s, a, dl);
-    else
-        render_bwd_tw<T, false>(s, a, dl);
+    if constexpr (T > 8) {
+        if ((int64_t)a.total_tiles * (T * T) <= (int64_t)per_cu * 256 * a.cus) {
+            render_bwd_tw<T, true>(s, a, dl);
+            return;
+        }
+    }
+    render_bwd_tw<T, false>(s, a, dl);
 }
 
 }  // namespace
